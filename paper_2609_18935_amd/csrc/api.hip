@@ -488,12 +488,25 @@ struct AttnLaunch {
 
 inline int64_t vt_head_tiles(int64_t rows) { return (rows + kAttnKeys - 1) / kAttnKeys; }
 
+// Key tiles that the shortest and the longest query tile of a context see.
+struct TileSpan {
+  int64_t lo, hi;
+};
+TileSpan tile_span(int64_t L_keep, int64_t T, int G) {
+  const int64_t first = std::min<int64_t>(T, (kAttnRows + G - 1) / G);   // tail tokens up to the first query tile's last row
+  return {(L_keep + first + kAttnKeys - 1) / kAttnKeys, (L_keep + T + kAttnKeys - 1) / kAttnKeys};
+}
+
 // Key-range splits of one context's attention. An attention workgroup holds a whole CU,
 // so a launch runs in waves of kCus workgroups. When every item of the launch has the
 // same surviving rows and tail (one context, or the attention layers of one context's
-// stack), the split count minimises (waves) x (time of one workgroup: its key tiles plus
-// a fixed part) plus the merge (a launch, and the partial outputs written and read back
-// once per split); about 3.8 us per 64-key tile of 256 rows at head_dim 256, 5 TB/s. With items of
+// stack), the split count minimises the launch's time plus the merge. The launch takes the
+// key tiles of its busiest CU (a refill's query tiles see from one key tile to all; they
+// run longest first, so the first item of a later wave follows the shortest of the wave
+// before it), about 3.8 us per 64-key tile of 256 rows and 12 us per wave (prologue and
+// epilogue) at head_dim 256; the merge 8 us and the partial outputs at 5 TB/s once per split.
+// Measured against it (16/2 heads of 256, no context): 4,096 tokens in 2 splits 209 us,
+// whole 246 us; 2,048 in 2 splits 97 us, in 3 splits 105 us. With items of
 // different lengths in the launch (whose waves do not line up) it takes enough splits
 // for the launch to fill the CUs. At least 4 key tiles per split, at most
 // kMaxAutoSplits (a decode-like tail of one token over 32K rows fills the chip with 128
@@ -509,13 +522,26 @@ int choose_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t ba
     const int64_t want = std::max<int64_t>(1, (kCus + base_items_total - 1) / std::max<int64_t>(1, base_items_total));
     return (int)std::min(want, max_s);
   }
-  const double tile_us = 3.8 * p->head_dim / 256.0;
+  const double tile_us = 3.8 * p->head_dim / 256.0, wave_us = 4.0 + 8.0 * p->head_dim / 256.0;
   const double split_us = (double)T * p->n_q_heads * p->head_dim * 4.0 / 5e6;
+  const TileSpan span = tile_span(L_keep, T, p->n_q_heads / p->n_kv_heads);
   double best = 0.0;
   int best_s = 1;
   for (int64_t s = 1; s <= max_s; ++s) {
     const int64_t waves = (base_items_total * s + kCus - 1) / kCus;
-    const double est = (double)waves * ((double)((n_kt + s - 1) / s) * tile_us + 5.0) + (s > 1 ? 5.0 + split_us * s : 0.0);
+    const int64_t longest = (span.hi + s - 1) / s, shortest = (span.lo + s - 1) / s;
+    // lengths fall evenly from longest to shortest; paired waves fill each other's gaps
+    double tiles = (double)longest;
+    if (waves > 1) {
+      const auto at = [&](int64_t wave) {
+        return (double)longest - (double)(longest - shortest) * (double)(wave * kCus) / (double)(base_items_total * s);
+      };
+      double sum = waves & 1 ? at(waves - 1) : 0.0;
+      for (int64_t w = 1; w < waves; w += 2) sum += 2.0 * at(w);
+      tiles = std::max(tiles, sum);
+    }
+    double est = tiles * tile_us + waves * wave_us + (s > 1 ? 8.0 + split_us * s : 0.0);
+    if (waves > 1 && longest > shortest) est *= 1.03;   // uneven items never pack quite as well
     if (s == 1 || est < best) {
       best = est;
       best_s = (int)s;
@@ -531,6 +557,16 @@ int choose_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t ba
 void plan_dies(const AttnArgs& a, int G, AttnOrder* o) {
   o->n_groups = 0;
   o->blocks = 0;
+  o->longest_first = 0;
+  if (a.n_seq == 1) {
+    // More than one wave of query tiles of different lengths: equal shares of the item
+    // order would give the dies of the early tiles little and those of the late ones most
+    // of the work (a refill of 8,191 tokens, 512 items of 4 to 128 key tiles: 791 us of
+    // attention, 525 us longest first). Near-equal tiles keep the shares, whose
+    // neighbours read one key range through one die's L2.
+    const TileSpan span = tile_span(a.seq[0].L_keep, a.seq[0].T, G);
+    o->longest_first = a.total_items > kCus && 8 * (span.hi - span.lo) > span.hi;
+  }
   if (a.n_seq < 2) return;
   struct Grp {
     int64_t cost;

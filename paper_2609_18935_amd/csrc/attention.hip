@@ -123,9 +123,17 @@ struct IntC {
   static constexpr int value = B;
 };
 
-// The item of this workgroup: by the launch's die table when it has one, else equal
-// shares of the item order per die.
-__device__ __forceinline__ int attn_item(const AttnOrder& o) {
+// The item of this workgroup: by the launch's die table when it has one, longest query
+// tiles first when the launch asks for it (one context: block b takes query tile
+// n_tiles - 1 - b / groups of group b % groups, so the tiles, and the work, spread over
+// the dies), else equal shares of the item order per die.
+__device__ __forceinline__ int attn_item(const AttnArgs& a, const AttnOrder& o) {
+  if (o.longest_first) {
+    const int groups = a.total_items / a.seq[0].n_tiles;
+    const int rank = blockIdx.x / groups;
+    if ((int)blockIdx.x >= a.total_items) return 0x7fffffff;
+    return ((int)blockIdx.x - rank * groups) * a.seq[0].n_tiles + rank;
+  }
   if (o.n_groups == 0) return xcd_remap(blockIdx.x, gridDim.x);
   const int x = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
   const int g0 = o.die_begin[x], g1 = o.die_begin[x + 1];
@@ -142,13 +150,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   constexpr int NDB = D / 32;               // 32-dim blocks of O^T
   constexpr int RC = D / 8;                 // 16-byte chunks of data per K row
 
-  const int item = attn_item(ord);
+  const int item = attn_item(a, ord);
   if (item >= a.total_items) return;
   int si = 0;
   while (si + 1 < a.n_seq && a.seq[si + 1].item_begin <= item) ++si;
   const AttnSeq& S = a.seq[si];
   int local = item - S.item_begin;
-  const int tile = __builtin_amdgcn_readfirstlane(local % S.n_tiles);
+  // a group's later query tiles see more keys: they run first where a die runs several waves
+  const int nth = local % S.n_tiles;
+  const int tile = __builtin_amdgcn_readfirstlane(ord.longest_first || ord.n_groups ? S.n_tiles - 1 - nth : nth);
   local /= S.n_tiles;
   const int split = __builtin_amdgcn_readfirstlane(local % S.n_splits);
   const int hkv = __builtin_amdgcn_readfirstlane(local / S.n_splits);

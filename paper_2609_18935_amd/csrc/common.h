@@ -253,7 +253,7 @@ struct AttnOrder {
   int32_t n_groups;                   // 0: equal item counts per die in item order (xcd_remap)
   int32_t blocks;                     // grid size
   int32_t die_begin[kXcds + 1];
-  int32_t pad;
+  int32_t longest_first;              // one context whose query tiles differ in length (n_groups is 0)
   uint16_t grp_item0[kMaxAttnGroups];
   uint16_t grp_end[kMaxAttnGroups];   // slots of the die up to and including group g
 };
