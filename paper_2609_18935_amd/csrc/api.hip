@@ -484,6 +484,7 @@ struct AttnLaunch {
   AttnOrder order;
   MergeArgs merge;
   int merge_rows;
+  bool short_tail;   // the short-tail kernel (no V^T tiles read)
 };
 
 inline int64_t vt_head_tiles(int64_t rows) { return (rows + kAttnKeys - 1) / kAttnKeys; }
@@ -620,6 +621,30 @@ void plan_dies(const AttnArgs& a, int G, AttnOrder* o) {
   o->blocks = most * kXcds;
 }
 
+// When a launch takes the short-tail kernel: its contexts have at most kShortMaxRows packed
+// query rows (T x query heads per KV head), in at most two row tiles, or the whole launch
+// is at most kShortWork units (32 rows x 32 keys), 8 per wave of the chip. The short kernel
+// takes about 1.7 us per unit and wave, the long one 3.8 us per 256 rows x 64 keys however
+// few of the rows are used, plus its prologue and the V^T tiles. Measured (16/2 heads of
+// 256, V^T copy current; short / long kernel, us a call): 1 token over 32,768 rows 27.2 /
+// 34.6, 8 tokens 33.4 / 36.8, 16 tokens 42.1 / 41.4, 32 tokens 58.2 / 49.7; over 12,000 rows 8
+// tokens 25.9 / 29.1, 32 tokens 33.1 / 40.5.
+constexpr int64_t kShortMaxRows = 256;
+constexpr int64_t kShortWork = 8192;
+
+// Key-range splits of one context in a short-tail launch, in which one workgroup per CU
+// reads an equal share of the launch's units (`work`); a workgroup's four waves take at
+// least one unit each. A context of up to two units per wave (four of shorter rows) is not
+// split: the merge launch would take longer.
+int short_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t work) {
+  if (p->kv_splits > 0) return p->kv_splits;
+  const int64_t units = (L_keep + T + kShortKeys - 1) / kShortKeys;
+  const int64_t per_wave = (units + 3) / 4;
+  if (per_wave <= (p->head_dim == 256 ? 2 : 4)) return 1;
+  const int64_t share = units * kCus / std::max<int64_t>(1, work);
+  return (int)std::max<int64_t>(1, std::min({share, per_wave, (int64_t)kMaxAutoSplits}));
+}
+
 int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* ws, const CallStatus& status,
                    std::vector<AttnLaunch>* out, size_t* ws_bytes) {
   const int Hq = p->n_q_heads, Hkv = p->n_kv_heads, D = p->head_dim, G = Hq / Hkv;
@@ -642,6 +667,14 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       uniform = uniform && items[i].T == first->T && items[i].L_keep == first->L_keep;
     }
     AttnLaunch L{};
+    int64_t rows_most = 0, short_work = 0;
+    for (size_t i = g0; i < g1; ++i) {
+      const int64_t rows = items[i].T * G;
+      rows_most = std::max(rows_most, rows);
+      short_work += Hkv * ((rows + kShortRows - 1) / kShortRows) *
+                    ((items[i].L_keep + items[i].T + kShortKeys - 1) / kShortKeys);
+    }
+    L.short_tail = rows_most <= 2 * kShortRows || (rows_most <= kShortMaxRows && short_work <= kShortWork);
     L.rope.n_q_heads = Hq;
     L.rope.n_kv_heads = Hkv;
     L.rope.head_dim = D;
@@ -658,21 +691,24 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       bf16_t* qh = it.q_hat;
       void* qh_ws = ar.take(sizeof(bf16_t) * it.T * Hq * D);
       if (!qh) qh = static_cast<bf16_t*>(qh_ws);
-      const int tiles = (int)((it.T * G + kAttnRows - 1) / kAttnRows);
-      const int splits = choose_splits(p, it.L_keep, it.T, base_items, uniform);
+      const int tile_rows = L.short_tail ? kShortRows : kAttnRows;
+      const int tiles = (int)((it.T * G + tile_rows - 1) / tile_rows);
+      const int splits = L.short_tail ? short_splits(p, it.L_keep, it.T, short_work)
+                                      : choose_splits(p, it.L_keep, it.T, base_items, uniform);
       // V^T tiles: refreshed in the layer's own copy from the first row it lacks, or all
-      // packed into the workspace
-      const int vt_end = (int)vt_head_tiles(it.L_keep + it.T);
-      _Float16* vt;
-      int vt_begin, head_tiles;
+      // packed into the workspace (the short-tail kernel reads none: nothing is packed)
+      int vt_end = (int)vt_head_tiles(it.L_keep + it.T);
+      _Float16* vt = nullptr;
+      int vt_begin = 0, head_tiles = 0;
       if (it.vt_cache) {
         vt = static_cast<_Float16*>(it.vt_cache);
         head_tiles = (int)vt_head_tiles(it.seq->capacity);
         vt_begin = (int)(std::min(it.vt_rows, it.L_keep) / kAttnKeys);
+      } else if (L.short_tail) {
+        vt_end = 0;
       } else {
         vt = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)Hkv * vt_end * D * kVtRow));
         head_tiles = vt_end;
-        vt_begin = 0;
       }
       _Float16* po = nullptr;
       float* pml = nullptr;
@@ -712,6 +748,8 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       s.q_hat = qh;
       s.k_cache = static_cast<const bf16_t*>(it.k_cache);
       s.vt = vt;
+      s.v_cache = static_cast<const bf16_t*>(it.v_cache);
+      s.check_range = it.vt_cache == nullptr;
       s.out = it.out;
       s.part_o = po;
       s.part_ml = pml;
@@ -731,14 +769,14 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
     L.merge.row_begin[L.merge.n_seq] = mrows;
     L.rope_tokens = tok;
     L.attn.total_items = item_total;
-    plan_dies(L.attn, G, &L.order);
+    if (!L.short_tail) plan_dies(L.attn, G, &L.order);
     L.pack.pack_items = pack_total;
     L.pack.status = status;
     L.merge_rows = mrows;
     {   // lanes per row piece: one per batch of 8 splits of the launch's largest split count
       int most = 1;
       for (int m = 0; m < L.merge.n_seq; ++m) most = std::max(most, (int)L.merge.seq[m].n_splits);
-      L.merge.split_lanes = most <= 8 ? 1 : most <= 16 ? 2 : most <= 32 ? 4 : 8;
+      L.merge.split_lanes = most <= 8 ? 1 : most <= 16 ? 2 : most <= 32 ? 4 : most <= 64 ? 8 : 16;
     }
     max_used = std::max(max_used, ar.used);
     if (L.rope.n_seq > 0) out->push_back(L);
@@ -779,7 +817,7 @@ int run_attention(const std::vector<AttnLaunch>& ls, int D, hipStream_t st, hipE
       if (int e = hip_check(hipStreamWaitEvent(st, gate, 0), "attention gate")) return e;
       gate = nullptr;
     }
-    if (int e = hip_check(timed("attention", st, [&] { return launch_attention(L.attn, L.order, D, st); }), "attention launch")) return e;
+    if (int e = hip_check(timed("attention", st, [&] { return L.short_tail ? launch_attention_short(L.attn, L.pack.status, D, st) : launch_attention(L.attn, L.order, D, st); }), "attention launch")) return e;
     if (L.merge_rows > 0)
       if (int e = hip_check(timed("attention_merge", st, [&] { return launch_attention_merge(L.merge, L.merge_rows, D, st); }), "merge launch")) return e;
   }

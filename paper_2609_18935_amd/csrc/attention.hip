@@ -39,7 +39,7 @@
 // A launch of one context gives every die an equal share of the items in this order;
 // a launch of several contexts, whose key ranges differ in length, places the groups
 // by a table: longest first, each on the die with the least work so far.
-#include "common.h"
+#include "attention_tile.h"
 
 namespace tu {
 
@@ -49,30 +49,6 @@ typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 
 constexpr int kBM = kAttnRows;
 constexpr int kBN = kAttnKeys;
-constexpr float kTau = 8.f;  // lazy-rescale threshold (log2 units): P < 2^8 fits f16
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-// s_waitcnt immediate that waits on the vector-memory counter only
-constexpr int vm_wait(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-
-// Fourth word of a raw buffer resource (32-bit data, no swizzle) on CDNA
-constexpr int kBufWord3 = 0x00020000;
-
-// Copies 16 bytes per lane from base + voff + soff to LDS (lane i writes lds + 16 i).
-// The resource covers `bytes` from base; lanes past it write zeros. base and bytes are
-// wave-uniform; reading them through readfirstlane lets the compiler see that, so the
-// resource stays in scalar registers (no per-lane loop around the load).
-__device__ __forceinline__ void dma16(const void* base, int bytes, uint32_t voff, uint32_t soff, void* lds) {
-  const uint64_t b = (uint64_t)base;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-  void* ub = (void*)(((uint64_t)hi << 32) | lo);
-  const __amdgpu_buffer_rsrc_t res =
-      __builtin_amdgcn_make_buffer_rsrc(ub, 0, __builtin_amdgcn_readfirstlane(bytes), kBufWord3);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)lds, 16, voff, soff, 0, 0);
-}
-
 // s_waitcnt immediate that waits on the LDS counter only
 constexpr int kLgkmWait0 = 15 | (7 << 4) | (0 << 8) | (3 << 14);
 
@@ -111,12 +87,6 @@ __shared__ __attribute__((aligned(16))) bf16_t g_ks0[kKStage];
 __shared__ __attribute__((aligned(16))) bf16_t g_ks1[kKStage];
 __shared__ __attribute__((aligned(16))) _Float16 g_vt0[kVStage];
 __shared__ __attribute__((aligned(16))) _Float16 g_vt1[kVStage];
-
-// Scales an MFMA accumulator (the rare move of the softmax reference max).
-__device__ __forceinline__ void scale_acc(f32x16& acc, float s) {
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] *= s;
-}
 
 template <int B>
 struct IntC {
@@ -421,7 +391,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 }
 
-// Log-sum-exp merge of the split partials: `split_lanes` (1, 2, 4 or 8) consecutive
+// Log-sum-exp merge of the split partials: `split_lanes` (1, 2, 4, 8 or 16) consecutive
 // lanes per 8 output dims of one (token, head) row. Lane l of a row's group takes the
 // splits l, l + split_lanes, ... in batches of 8 whose loads are all in flight
 // together (the running max and sums move between batches); the lanes' partial
@@ -531,7 +501,7 @@ hipError_t launch_attention(const AttnArgs& a, const AttnOrder& o, int head_dim,
 
 hipError_t launch_attention_merge(const MergeArgs& a, int total_rows, int head_dim, hipStream_t s) {
   if (total_rows <= 0) return hipSuccess;
-  if (a.split_lanes != 1 && a.split_lanes != 2 && a.split_lanes != 4 && a.split_lanes != 8) return hipErrorInvalidValue;
+  if (a.split_lanes < 1 || a.split_lanes > 16 || (a.split_lanes & (a.split_lanes - 1))) return hipErrorInvalidValue;
   const long threads = (long)total_rows * (head_dim / 8) * a.split_lanes;
   const int blocks = (int)((threads + 255) / 256);
   if (head_dim == 256)

@@ -29,6 +29,8 @@ constexpr int kFlagStride = 32;   // compaction stripe counters sit one per 128-
 constexpr int kGatherStripeBytes = 256 * 16 * 16;  // threads x vectors x 16 B
 constexpr int kAttnRows = 256;  // packed query rows per attention workgroup
 constexpr int kAttnKeys = 64;   // keys per attention K/V tile
+constexpr int kShortRows = 32;  // packed query rows per short-tail attention workgroup
+constexpr int kShortKeys = 32;  // keys of a short-tail unit
 constexpr int kVtRow = kAttnKeys + 8;  // f16 per row of a packed V^T tile (64 keys + pad)
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) {
@@ -218,16 +220,19 @@ struct PackArgs {
 struct AttnSeq {
   const bf16_t* q_hat;   // [T][Hq][D]
   const bf16_t* k_cache; // [cap][Hkv][D]
-  const _Float16* vt;    // [Hkv][head_tiles][D * kVtRow] packed f16 V^T tiles
+  const _Float16* vt;    // [Hkv][head_tiles][D * kVtRow] packed f16 V^T tiles (long kernel)
+  const bf16_t* v_cache; // [cap][Hkv][D] (short kernel)
   float* out;            // [T][Hq][D]
   _Float16* part_o;      // [splits][T*Hq][D] normalised split outputs (unused when splits == 1)
   float* part_ml;        // [splits][T*Hq][2] (reference max in log2 units, sum)
   int32_t L_keep;
   int32_t T;
-  int32_t n_tiles;       // ceil(T*G / kAttnRows)
+  int32_t n_tiles;       // ceil(T*G / kAttnRows), or / kShortRows for the short kernel
   int32_t n_splits;
   int32_t item_begin;    // first attention workgroup of this context
   int32_t head_tiles;    // tiles per KV head in vt
+  int32_t check_range;   // short kernel: report values beyond f16 (no packing launch does)
+  int32_t pad;
 };
 
 struct AttnArgs {
@@ -262,7 +267,7 @@ struct MergeArgs {
   AttnSeq seq[kMaxSeqPerLaunch];
   int32_t n_seq;
   int32_t n_q_heads;
-  int32_t split_lanes;   // lanes per 8 output dims of a row (1, 2, 4 or 8), each a share of the splits
+  int32_t split_lanes;   // lanes per 8 output dims of a row (1, 2, 4, 8 or 16), each a share of the splits
   int32_t row_begin[kMaxSeqPerLaunch + 1];  // prefix of T*Hq over contexts
 };
 
@@ -408,6 +413,7 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
 // RoPE + append of the tail tokens and the V^T packing of every key tile, one launch
 hipError_t launch_stage(const RopeArgs& r, int rope_tokens, const PackArgs& p, int head_dim, hipStream_t s);
 hipError_t launch_attention(const AttnArgs& a, const AttnOrder& o, int head_dim, hipStream_t s);
+hipError_t launch_attention_short(const AttnArgs& a, const CallStatus& status, int head_dim, hipStream_t s);
 hipError_t launch_relocate(const RelocArgs& a, hipStream_t s);
 hipError_t launch_probe(const ProbeArgs& a, hipStream_t s);
 hipError_t launch_group_mass(const GroupArgs& a, hipStream_t s);

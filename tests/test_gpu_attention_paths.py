@@ -44,3 +44,71 @@ def test_longest_first_order(Hq, Hkv, D, L, T, splits):
     case = _run(synth.AttnShape(Hq, Hkv, D), L, T, splits)
     ref = case.oracle([], L)
     assert_close(case.out.cpu().numpy(), ref["out"], "longest-first attention")
+
+
+# The short-tail kernel: one to eight row tiles of 32, contexts of none to a few rows per
+# wave and of many, ragged last units (32 keys) and row tiles, every head size, group
+# sizes that leave row tiles partly empty, forced and automatic splits.
+@pytest.mark.parametrize("Hq,Hkv,D,rdim,L,T,splits", [
+    (16, 2, 256, 256, 0, 1, 0),
+    (16, 2, 256, 256, 31, 1, 0),
+    (16, 2, 256, 256, 4097, 4, 0),
+    (16, 2, 256, 256, 4000, 32, 0),
+    (16, 2, 256, 256, 700, 5, 64),
+    (32, 8, 128, 64, 1999, 9, 0),
+    (3, 3, 128, 128, 5000, 63, 2),
+    (16, 4, 64, 64, 9001, 64, 0),
+    (20, 4, 64, 32, 250, 7, 1),
+])
+def test_short_tail(Hq, Hkv, D, rdim, L, T, splits):
+    print(f"[case] short tail Hq={Hq} Hkv={Hkv} D={D} rdim={rdim} L={L} T={T} splits={splits}", flush=True)
+    case = _run(synth.AttnShape(Hq, Hkv, D, rotary_dim=rdim), L, T, splits)
+    ref = case.oracle([], L)
+    assert_close(case.out.cpu().numpy(), ref["out"], "short-tail attention")
+
+
+@pytest.mark.parametrize("vt", [False, True])
+def test_short_tail_many_contexts_in_one_call(vt):
+    """Seven contexts of different lengths, three tokens each or fewer, in one launch."""
+    shape = synth.AttnShape(16, 2, 128)
+    sizes = [(0, 1), (33, 3), (2500, 2), (64, 1), (700, 3), (1, 2), (6000, 1)]
+    print(f"[case] short tails of {len(sizes)} contexts, V^T copies {vt}", flush=True)
+    cases = [AttnCase(shape, 23, 0, 0, L, T, char=i) for i, (L, T) in enumerate(sizes)]
+    ctxs, vts = [], []
+    for c in cases:
+        ctx = tu.Context(c.capacity, device=DEV)
+        ctx.pos[:c.L_old] = torch.arange(c.L_old, dtype=torch.int32, device=DEV)
+        ctx.set_metadata([(0, c.L_old)] if c.L_old else [], c.L_old)
+        v = tu.new_vt_cache(c.capacity, shape.n_kv_heads, shape.head_dim, DEV)
+        if vt and c.L_old:
+            tu.refresh_vt_cache(ctx, [c.v_cache], [v])
+        ctxs.append(ctx)
+        vts.append(v)
+    out = torch.full((sum(T for _, T in sizes), shape.n_q_heads, shape.head_dim), float("nan"), device=DEV)
+    layer = tu.LayerIO(tu.TU_LAYER_ATTN, torch.cat([c.q for c in cases]), torch.cat([c.k for c in cases]),
+                       torch.cat([c.v for c in cases]), out, k_cache=[c.k_cache for c in cases],
+                       v_cache=[c.v_cache for c in cases], vt_cache=vts if vt else None)
+    p = tu.attn_params(shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rdim, shape.rope_theta,
+                       shape.softmax_scale)
+    up = tu.update_layer_stack(ctxs, [[] for _ in sizes], [T for _, T in sizes], [layer], p)
+    torch.cuda.synchronize()
+    assert tu.workspace_faults(up.workspace) == 0
+    at = 0
+    for i, (c, (L, T)) in enumerate(zip(cases, sizes)):
+        assert ctxs[i].vt_rows == L + T
+        assert_close(out[at:at + T].cpu().numpy(), c.oracle([], L)["out"], f"context {i} (L={L}, T={T})")
+        at += T
+
+
+def test_short_tail_flags_values_beyond_f16():
+    """A value of magnitude 1e5 in the last cache row, or in the tail, sets TU_FAULT_RANGE."""
+    shape = synth.AttnShape(16, 2, 256)
+    for where in ("cache", "tail"):
+        print(f"[case] short tail, value 1e5 in the {where}", flush=True)
+        c = AttnCase(shape, 24, 0, 0, 333, 2)
+        (c.v_cache if where == "cache" else c.v)[332 if where == "cache" else 1, 1, 7] = 1.0e5
+        ctx = tu.Context(c.capacity, device=DEV)
+        ctx.pos[:333] = torch.arange(333, dtype=torch.int32, device=DEV)
+        ctx.set_metadata([(0, 333)], 333)
+        ws = tu.tail_prefill_attention(ctx, c.k_cache, c.v_cache, tu.attn_params(16, 2, 256), c.q, c.k, c.v, c.out)
+        assert tu.workspace_faults(ws) & tu.TU_FAULT_RANGE
