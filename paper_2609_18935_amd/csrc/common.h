@@ -285,6 +285,9 @@ struct DeltaSeq {
   int32_t pad;
 };
 
+constexpr int kStepTokens = 32;   // longest tail of the token-by-token delta kernel
+constexpr int kStepRows = 16;     // state rows of one of its workgroups
+
 struct DeltaArgs {
   DeltaSeq seq[kMaxSeqPerDelta];
   int32_t n_seq;
@@ -293,6 +296,8 @@ struct DeltaArgs {
   int32_t total_chunks;
   float scale;
   int32_t n_slices;      // d_v slices per value head in the chain kernel
+  int32_t step;          // every tail is at most kStepTokens: the token-by-token kernel (no workspace)
+  int32_t pad;
   CallStatus status;     // kFaultRange when an f16 operand overflows
   _Float16* ws_w;        // [chunks][Hv][C][dk]  W = T diag(beta 2^lg) K, d in operand order
   _Float16* ws_tv;       // [chunks][Hv][C][C]   T diag(beta)
@@ -423,6 +428,7 @@ int conv_blocks(ConvJob& j, int block_begin);   // sets block_begin / n_cblocks,
 hipError_t launch_short_conv(const ConvArgs& a, int blocks, int width, hipStream_t s);
 hipError_t launch_attention_merge(const MergeArgs& a, int total_rows, int head_dim, hipStream_t s);
 hipError_t launch_delta_prep(const DeltaArgs& a, int d, int chunk, hipStream_t s);
+hipError_t launch_delta_step(const DeltaArgs& a, int d, hipStream_t s);
 hipError_t launch_delta_chain(const DeltaArgs& a, int d, int chunk, hipStream_t s);
 
 }  // namespace tu
