@@ -1562,14 +1562,12 @@ int short_conv_continue_batch(const tu_conv_tensor* tensors, int32_t n, int32_t 
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   ConvArgs a{};
-  int blocks = 0;
   auto flush = [&]() -> int {
     if (a.n_jobs == 0) return TU_OK;
-    if (int e = hip_check(timed("short_conv", st, [&] { return launch_short_conv(a, blocks, width, st); }),
+    if (int e = hip_check(timed("short_conv", st, [&] { return launch_short_conv(a, width, st); }),
                           "short-conv launch"))
       return e;
     a = ConvArgs{};
-    blocks = 0;
     return TU_OK;
   };
   for (int i = 0; i < n; ++i) {
@@ -1583,7 +1581,6 @@ int short_conv_continue_batch(const tu_conv_tensor* tensors, int32_t n, int32_t 
     j.T = (int32_t)t.T;
     j.C = t.channels;
     j.act = activation == TU_CONV_SILU;
-    blocks += conv_blocks(j, blocks);
     if (a.n_jobs == kMaxConvJobs)
       if (int e = flush()) return e;
   }

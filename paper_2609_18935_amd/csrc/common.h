@@ -424,8 +424,7 @@ hipError_t launch_probe(const ProbeArgs& a, hipStream_t s);
 hipError_t launch_group_mass(const GroupArgs& a, hipStream_t s);
 hipError_t launch_group_final(const GroupArgs& a, hipStream_t s);
 hipError_t launch_tv(const TvArgs& a, hipStream_t s);
-int conv_blocks(ConvJob& j, int block_begin);   // sets block_begin / n_cblocks, returns the job's workgroups
-hipError_t launch_short_conv(const ConvArgs& a, int blocks, int width, hipStream_t s);
+hipError_t launch_short_conv(ConvArgs& a, int width, hipStream_t s);   // sets each job's block_begin, n_cblocks
 hipError_t launch_attention_merge(const MergeArgs& a, int total_rows, int head_dim, hipStream_t s);
 hipError_t launch_delta_prep(const DeltaArgs& a, int d, int chunk, hipStream_t s);
 hipError_t launch_delta_step(const DeltaArgs& a, int d, hipStream_t s);

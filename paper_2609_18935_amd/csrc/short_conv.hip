@@ -4,7 +4,7 @@
 //     y_t[c] = act( sum_{j<W} w[c][j] * xt[t + j][c] ),   xt = (W-1 carried rows, then x)
 // act = SiLU or identity; the carried state becomes the last W-1 rows of xt.
 //
-// One thread per 8 channels (16-byte loads and stores) and a block of kConvTokens
+// One thread per 8 channels (16-byte loads and stores) and a block of 8 or 4
 // tokens: it requests the block's rows and the W-1 rows before it all at once (one
 // memory round trip), then forms each output from a window of W rows in registers. Products are accumulated in
 // fp32 in tap order and rounded to bf16 (round to nearest even). Only the first
@@ -18,7 +18,14 @@ namespace tu {
 namespace {
 
 constexpr int kConvThreads = 256;
-constexpr int kConvTokens = 8;    // tokens per block (>= W - 1, so only block 0 reads the state)
+// Tokens per block (at least W - 1, so only block 0 reads the state). A thread's outputs take
+// longer than its loads when the launch leaves about one wave per SIMD, so small launches
+// take blocks of half the tokens; large ones keep 8, with fewer rows read twice (q, k, v
+// of 2,048, 2,048 and 4,096 channels, W = 4: 300 tokens 8.4 -> 7.1 us, 1,200 tokens 14.6 ->
+// 13.1; 2,400 tokens and more keep the 8-token blocks).
+constexpr int kConvTokens = 8;
+constexpr int kConvTokensSmall = 4;
+constexpr int kConvSmallBlocks = 1024;   // workgroups of 8-token blocks below which a launch is small
 
 __device__ __forceinline__ void unpack8(u32x4 w, float (&f)[8]) {
 #pragma unroll
@@ -28,7 +35,7 @@ __device__ __forceinline__ void unpack8(u32x4 w, float (&f)[8]) {
   }
 }
 
-template <int W>
+template <int W, int NT>
 __global__ __launch_bounds__(kConvThreads) void k_short_conv(ConvArgs a) {
   int ji = 0;
   while (ji + 1 < a.n_jobs && a.job[ji + 1].block_begin <= (int)blockIdx.x) ++ji;
@@ -38,8 +45,8 @@ __global__ __launch_bounds__(kConvThreads) void k_short_conv(ConvArgs a) {
   const int cg = (local - tb * J.n_cblocks) * kConvThreads + threadIdx.x;   // 8-channel group
   if (8 * cg >= J.C) return;
   const int C = J.C;
-  const int t0 = tb * kConvTokens;
-  const int t1 = min(J.T, t0 + kConvTokens);
+  const int t0 = tb * NT;
+  const int t1 = min(J.T, t0 + NT);
 
   float wf[W][8];
   {
@@ -53,11 +60,11 @@ __global__ __launch_bounds__(kConvThreads) void k_short_conv(ConvArgs a) {
       for (int e = 0; e < 8; ++e) wf[(8 * q + e) % W][(8 * q + e) / W] = tmp[e];
     }
   }
-  // rows t0 .. t0 + kConvTokens + W - 2 of xt (this thread's 8 channels), all requested
+  // rows t0 .. t0 + NT + W - 2 of xt (this thread's 8 channels), all requested
   // before any is used
   const bf16_t* __restrict__ xs = J.x;
   const bf16_t* __restrict__ ss = J.state;
-  constexpr int R = kConvTokens + W - 1;
+  constexpr int R = NT + W - 1;
   u32x4 raw[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(kConvThreads) void k_short_conv(ConvArgs a) {
 #pragma unroll
   for (int r = 0; r < W - 1; ++r) old[r] = raw[r];   // the carried rows when t0 == 0
 #pragma unroll
-  for (int k = 0; k < kConvTokens; ++k) {
+  for (int k = 0; k < NT; ++k) {
     const int t = t0 + k;
     if (t >= t1) break;
     float win[W][8];
@@ -115,26 +122,45 @@ __global__ __launch_bounds__(kConvThreads) void k_short_conv(ConvArgs a) {
 
 }  // namespace
 
-int conv_blocks(ConvJob& j, int block_begin) {
+namespace {
+
+int blocks_of(ConvJob& j, int tokens, int block_begin) {
   j.block_begin = block_begin;
   j.n_cblocks = (j.C / 8 + kConvThreads - 1) / kConvThreads;
-  return (int)((j.T + kConvTokens - 1) / kConvTokens) * j.n_cblocks;
+  return (j.T + tokens - 1) / tokens * j.n_cblocks;
 }
 
-hipError_t launch_short_conv(const ConvArgs& a, int blocks, int width, hipStream_t s) {
+template <int W>
+hipError_t conv_for(ConvArgs& a, hipStream_t s) {
+  int blocks = 0;
+  for (int i = 0; i < a.n_jobs; ++i) blocks += blocks_of(a.job[i], kConvTokens, blocks);
   if (blocks <= 0) return hipSuccess;
+  if constexpr (W - 1 <= kConvTokensSmall) {
+    if (blocks < kConvSmallBlocks) {
+      blocks = 0;
+      for (int i = 0; i < a.n_jobs; ++i) blocks += blocks_of(a.job[i], kConvTokensSmall, blocks);
+      hipLaunchKernelGGL((k_short_conv<W, kConvTokensSmall>), dim3(blocks), dim3(kConvThreads), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_short_conv<W, kConvTokens>), dim3(blocks), dim3(kConvThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_short_conv(ConvArgs& a, int width, hipStream_t s) {
   switch (width) {
-    case 1: hipLaunchKernelGGL(k_short_conv<1>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_short_conv<2>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 3: hipLaunchKernelGGL(k_short_conv<3>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 4: hipLaunchKernelGGL(k_short_conv<4>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 5: hipLaunchKernelGGL(k_short_conv<5>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 6: hipLaunchKernelGGL(k_short_conv<6>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 7: hipLaunchKernelGGL(k_short_conv<7>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
-    case 8: hipLaunchKernelGGL(k_short_conv<8>, dim3(blocks), dim3(kConvThreads), 0, s, a); break;
+    case 1: return conv_for<1>(a, s);
+    case 2: return conv_for<2>(a, s);
+    case 3: return conv_for<3>(a, s);
+    case 4: return conv_for<4>(a, s);
+    case 5: return conv_for<5>(a, s);
+    case 6: return conv_for<6>(a, s);
+    case 7: return conv_for<7>(a, s);
+    case 8: return conv_for<8>(a, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace tu
