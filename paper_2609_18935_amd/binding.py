@@ -165,8 +165,11 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        # NULL is the default stream; torch's current stream when a GPU is present
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        # NULL is the default stream; torch's current stream when a GPU is present, by its
+        # handle (0.2 us; the stream object torch.cuda.current_stream() makes takes 2.8)
+        if not torch.cuda.is_available():
+            return None
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
