@@ -50,10 +50,12 @@ def _resources(remarks: str) -> dict:
     return out
 
 
-# Per-file options. The attention kernel runs two waves per SIMD (256 registers each):
-# with its MFMA accumulators in ordinary vector registers the compiler may use the
-# whole budget, instead of splitting it in equal accumulator and vector halves.
-FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]}
+# Per-file options: MFMA accumulators in ordinary vector registers. The attention kernel runs
+# two waves per SIMD (256 registers each) and may then use the whole budget, instead of
+# splitting it in equal accumulator and vector halves; the delta rule's direct chain is
+# spared 90 register moves per chunk.
+_VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]
+FILE_FLAGS = {"attention.hip": _VGPR_MFMA, "delta.hip": _VGPR_MFMA}
 
 
 def _compile(src: str):

@@ -844,6 +844,14 @@ struct DeltaItem {
 // the row products instead: 36 items, 16 tokens 73 us (chunked 89), 24 tokens 99 us (89).
 int64_t step_tokens(int64_t heads) { return heads <= kCus / 2 ? kStepTokens : kStepTokens / 2; }
 
+// 16-column blocks of S (items x value heads x d / 16) up to which a delta launch takes the
+// direct chain: one workgroup per CU. One layer of 32 heads of 128, chunk 64 (staged /
+// direct chain, between events): 512 tokens 22.9 / 15.1 us, 2,048 tokens 65 / 40 us, 8,191
+// tokens 265 / 179 us; two layers, 2,048 tokens 72 / 74 us (before its last trims); every
+// block reads the head's matrices, which the staged chain shares between up to four, so
+// eight layers take 205 / 466 us.
+constexpr int64_t kDirectBlocks = kCus;
+
 int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, void* ws, const CallStatus& status,
                std::vector<DeltaArgs>* out, size_t* ws_bytes) {
   const int C = p->chunk, Hv = p->n_v_heads, DK = p->d_k;
@@ -853,7 +861,7 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
     const size_t g1 = std::min(items.size(), g0 + kMaxSeqPerDelta);
     int n_active = 0;
     for (size_t i = g0; i < g1; ++i) n_active += items[i].T > 0;
-    // slice d_v (16 rows of S per owner wave of the chain) into as few workgroups per
+    // the staged chain: slice d_v (16 rows of S per owner wave) into as few workgroups per
     // head as give half the CUs one (the rest serve the attention layers running
     // beside the delta layers)
     int dvs = std::min(DK, 64);
@@ -862,7 +870,8 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
     a.n_k_heads = p->n_k_heads;
     a.n_v_heads = Hv;
     a.scale = p->scale;
-    a.n_slices = DK / dvs;
+    a.direct = (int64_t)n_active * Hv * (DK / 16) <= kDirectBlocks;
+    a.n_slices = a.direct ? DK / 16 : DK / dvs;
     a.status = status;
     int64_t longest = 0;
     for (size_t i = g0; i < g1; ++i) longest = std::max(longest, items[i].T);
@@ -891,7 +900,7 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
     }
     Arena ar(ws);
     a.ws_w = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * DK));
-    a.ws_tv = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * C));
+    a.ws_tv = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * std::max(C, 32)));
     a.ws_p = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * std::max(C, 32)));
     a.ws_dec = static_cast<float*>(ar.take(sizeof(float) * (size_t)chunks * Hv * 2 * C));
     a.ws_q = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * p->n_k_heads * C * DK));

@@ -297,10 +297,11 @@ struct DeltaArgs {
   float scale;
   int32_t n_slices;      // d_v slices per value head in the chain kernel
   int32_t step;          // every tail is at most kStepTokens: the token-by-token kernel (no workspace)
-  int32_t pad;
+  int32_t direct;        // the chain reads its operands straight from the workspace (few heads)
   CallStatus status;     // kFaultRange when an f16 operand overflows
+  // matrices of a chunk, in operand fragments (16 rows x 32 positions) as the chain reads them
   _Float16* ws_w;        // [chunks][Hv][C][dk]  W = T diag(beta 2^lg) K, d in operand order
-  _Float16* ws_tv;       // [chunks][Hv][C][C]   T diag(beta)
+  _Float16* ws_tv;       // [chunks][Hv][C][max(C, 32)]  T diag(beta)
   _Float16* ws_p;        // [chunks][Hv][C][max(C, 32)]  scale lower(G .* Q K^T), operand order
   float* ws_dec;         // [chunks][Hv][2][C]  decay factors 2^(lg_last - lg_s) and 2^lg_s
   _Float16* ws_q;        // [chunks][Hk][C][dk]  q in f16, d in operand order

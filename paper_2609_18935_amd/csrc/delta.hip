@@ -72,6 +72,16 @@ __device__ __forceinline__ int perm32(int x) {
   return (x & ~31) | (8 * (a & 3) + 4 * (a >> 2) + (x & 3));
 }
 
+// The workspace holds the chain's matrices (W, P, T_v, q, k^T) as MFMA operand fragments:
+// 16 rows x 32 positions of the contracted index, lane l = 16 g + r of a wave taking the 8
+// positions 8 g .. 8 g + 7 of row r as one 16-byte vector, 64 vectors (1 KB) in lane order.
+// Offset of (row, pos) in a matrix of NK fragments per row block; pos of 4 or 8
+// consecutive elements stays contiguous.
+template <int NK>
+__device__ __forceinline__ int frag_at(int row, int pos) {
+  return (((row >> 4) * NK + (pos >> 5)) * 64 + ((pos >> 3) & 3) * 16 + (row & 15)) * 8 + (pos & 7);
+}
+
 // The last sequence whose first chunk is at or before c (chunk_begin is non-decreasing
 // and starts at 0): a binary search, about log2(n_seq) dependent loads.
 __device__ __forceinline__ int find_seq_by_chunk(const DeltaArgs& a, int c) {
@@ -104,6 +114,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
   constexpr int KP = DK + 8;     // pitch of [C][DK] bf16 tiles
   constexpr int CT = C + 8;      // pitch of f16 tiles with the chunk index contiguous
   constexpr int CC = C < 32 ? 32 : C;   // row length of P in the workspace (padded)
+  constexpr int NKD = DK / 32, NKS = CC / 32;   // fragments per row block over d, over the chunk index
   constexpr int TRI = NB * (NB + 1) / 2 * 16 * kTriPitch;   // floats of a lower-block-triangular matrix
   // Three regions whose arrays have disjoint lifetimes (barriers separate the last reads
   // of one from the first writes of the next), 48 KB at C = 64, d = 128, so that three
@@ -239,7 +250,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
         big = fmaxf(big, fabsf(x));
         pv[e] = (_Float16)x;
       }
-      *(f16x4*)&Pg[r * CC + perm32(i0)] = pv;
+      *(f16x4*)&Pg[frag_at<NKS>(r, perm32(i0))] = pv;
     } else {
       const float br = bt[r];
       f32x4 mv;
@@ -268,13 +279,13 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
         hq[2 * q] = (_Float16)x0;
         hq[2 * q + 1] = (_Float16)x1;
       }
-      *(f16x8*)&Qg[r * DK + 8 * v8] = hq;
+      *(f16x8*)&Qg[frag_at<NKD>(r, 8 * v8)] = hq;
     }
   }
   // zero the upper blocks of P and the padding of its rows
   for (int e = tid; e < C * CC / 4; e += NT) {
     const int r = e / (CC / 4), i = (e - r * (CC / 4)) * 4;
-    if (i >= C || (i >> 4) > (r >> 4)) *(uint2*)&Pg[r * CC + perm32(i)] = uint2{0, 0};
+    if (i >= C || (i >> 4) > (r >> 4)) *(uint2*)&Pg[frag_at<NKS>(r, perm32(i))] = uint2{0, 0};
   }
   // the chain's decay factors: to the chunk's end, and from its start
   if (tid < C) {
@@ -343,9 +354,13 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
 
   // ---- phase 5: T diag(beta 2^lg) (f16, LDS) and T_v = T diag(beta) (f16, workspace),
   // zero above the diagonal blocks (whose entries of T were never written); k^T in f16
-  _Float16* Tvg = a.ws_tv + slot * C * C;
-  for (int e = tid; e < C * C / 4; e += NT) {
-    const int r = e / (C / 4), i0 = (e - r * (C / 4)) * 4;
+  _Float16* Tvg = a.ws_tv + slot * C * CC;
+  for (int e = tid; e < C * CC / 4; e += NT) {
+    const int r = e / (CC / 4), i0 = (e - r * (CC / 4)) * 4;
+    if (CC > C && i0 >= C) {   // the padding to a whole MFMA step
+      *(uint2*)&Tvg[frag_at<NKS>(r, i0)] = uint2{0, 0};
+      continue;
+    }
     f16x4 hw, hv;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -357,7 +372,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
       hv[q] = (_Float16)xv;
     }
     *(f16x4*)&Twh[r][i0] = hw;
-    *(f16x4*)&Tvg[r * C + i0] = hv;
+    *(f16x4*)&Tvg[frag_at<NKS>(r, i0)] = hv;
   }
   // k^T in f16 over the dead M, from the k rows read again (from L2: phase 0 read them)
   for (int e = tid; e < (C / 2) * (DK / 8); e += NT) {
@@ -388,7 +403,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
       const uint2 z2 = {0, 0};
       const uint2 lo = s0 < C ? *(const uint2*)&Kt[d][s0] : z2;
       const uint2 hi = s0 + 16 < C ? *(const uint2*)&Kt[d][s0 + 16] : z2;
-      *(u32x4*)&Kg[d * CC + 8 * v8] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+      *(u32x4*)&Kg[frag_at<NKS>(d, 8 * v8)] = u32x4{lo[0], lo[1], hi[0], hi[1]};
     }
   }
   _Float16* Wg = a.ws_w + slot * C * DK;
@@ -409,7 +424,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
     }
     big = fmaxf(big, max_abs4(o));
     const f16x4 wv = {(_Float16)o[0], (_Float16)o[1], (_Float16)o[2], (_Float16)o[3]};
-    *(f16x4*)&Wg[(16 * rb + l16) * DK + perm32(16 * db + 4 * g4)] = wv;
+    *(f16x4*)&Wg[frag_at<NKD>(16 * rb + l16, perm32(16 * db + 4 * g4))] = wv;
   }
   if (big > kF16Max) status_raise(a.status, kFaultRange);
 }
@@ -450,7 +465,7 @@ __global__ __launch_bounds__(kChainThreads) void k_delta_chain(DeltaArgs a) {
   constexpr int NKS = CC / 32;                  // MFMA steps over the chunk index
   // producer work per chunk: 16-byte vectors of q, k^T, W, P, T_v (copied as the prep
   // wrote them); 2-row x 8-column items of the v slice (converted and transposed)
-  constexpr int VQ = C * DK / 8, VK = DK * CC / 8, VW = C * DK / 8, VP = C * CC / 8, VT = C * C / 8;
+  constexpr int VQ = C * DK / 8, VK = DK * CC / 8, VW = C * DK / 8, VP = C * CC / 8, VT = C * CC / 8;
   constexpr int NVI = (C / 2) * (DVS / 8);
   // The owners finish their part of a chunk first, so with four owners they copy W, P
   // and T_v of the next chunk (loads issued before their products, stores after), with
@@ -482,14 +497,12 @@ __global__ __launch_bounds__(kChainThreads) void k_delta_chain(DeltaArgs a) {
   const int p = tid - 64 * NO;                  // producer thread index
   float big = 0.f;   // largest magnitude this thread rounds to f16
 
-  // chunk-index padding of T_v and the v slice (C = 16 only) stays zero for the whole
-  // kernel (k^T comes padded from the workspace)
+  // chunk-index padding of the v slice (C = 16 only) stays zero for the whole kernel (the
+  // other operands come padded from the workspace)
   if (C < 32) {
-    for (int e = tid; e < 2 * (C + DVS) * 16; e += NT) {
-      const int b = e / ((C + DVS) * 16), rest = e - b * (C + DVS) * 16;
-      const int row = rest / 16, x = C + (rest % 16);
-      if (row < C) stg[b].Tv[row][x] = (_Float16)0.f;
-      else stg[b].Vt[row - C][x] = (_Float16)0.f;
+    for (int e = tid; e < 2 * DVS * 16; e += NT) {
+      const int b = e / (DVS * 16), rest = e - b * DVS * 16;
+      stg[b].Vt[rest / 16][C + (rest % 16)] = (_Float16)0.f;
     }
   }
 
@@ -506,29 +519,32 @@ __global__ __launch_bounds__(kChainThreads) void k_delta_chain(DeltaArgs a) {
   auto fetch_pt = [&](int lc, int x, int n) {
     const long slot = (long)(S.chunk_begin + lc) * Hv + h;
     const u32x4* P4 = (const u32x4*)(a.ws_p + slot * C * CC);
-    const u32x4* T4 = (const u32x4*)(a.ws_tv + slot * C * C);
+    const u32x4* T4 = (const u32x4*)(a.ws_tv + slot * C * CC);
 #pragma unroll
     for (int j = 0; j < RP; ++j) rp[j] = x + n * j < VP ? P4[x + n * j] : z4;
 #pragma unroll
     for (int j = 0; j < RT; ++j) rt[j] = x + n * j < VT ? T4[x + n * j] : z4;
   };
+  // row and first column of vector e of a matrix of nk fragments per row block
+  auto vrow = [](int e, int nk) { return (e >> 6) / nk * 16 + (e & 15); };
+  auto vcol = [](int e, int nk) { return (e >> 6) % nk * 32 + ((e >> 4) & 3) * 8; };
   auto put_w = [&](Stage& B, int x, int n) {
 #pragma unroll
     for (int j = 0; j < RW; ++j) {
       const int e = x + n * j;
-      if (e < VW) *(u32x4*)&B.W[e / (DK / 8)][8 * (e % (DK / 8))] = rw[j];
+      if (e < VW) *(u32x4*)&B.W[vrow(e, NKD)][vcol(e, NKD)] = rw[j];
     }
   };
   auto put_pt = [&](Stage& B, int x, int n) {
 #pragma unroll
     for (int j = 0; j < RP; ++j) {
       const int e = x + n * j;
-      if (e < VP) *(u32x4*)&B.P[e / (CC / 8)][8 * (e % (CC / 8))] = rp[j];
+      if (e < VP) *(u32x4*)&B.P[vrow(e, NKS)][vcol(e, NKS)] = rp[j];
     }
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
       const int e = x + n * j;
-      if (e < VT) *(u32x4*)&B.Tv[e / (C / 8)][8 * (e % (C / 8))] = rt[j];
+      if (e < VT) *(u32x4*)&B.Tv[vrow(e, NKS)][vcol(e, NKS)] = rt[j];
     }
   };
   auto fetch = [&](int lc) {
@@ -558,12 +574,12 @@ __global__ __launch_bounds__(kChainThreads) void k_delta_chain(DeltaArgs a) {
 #pragma unroll
     for (int j = 0; j < RQ; ++j) {
       const int e = p + NP * j;
-      if (e < VQ) *(u32x4*)&B.Q[e / (DK / 8)][8 * (e % (DK / 8))] = rq[j];
+      if (e < VQ) *(u32x4*)&B.Q[vrow(e, NKD)][vcol(e, NKD)] = rq[j];
     }
 #pragma unroll
     for (int j = 0; j < RK; ++j) {
       const int e = p + NP * j;
-      if (e < VK) *(u32x4*)&B.Kt[e / (CC / 8)][8 * (e % (CC / 8))] = rk[j];
+      if (e < VK) *(u32x4*)&B.Kt[vrow(e, NKS)][vcol(e, NKS)] = rk[j];
     }
 #pragma unroll
     for (int j = 0; j < RV; ++j) {
@@ -691,6 +707,305 @@ __global__ __launch_bounds__(kChainThreads) void k_delta_chain(DeltaArgs a) {
   if (big > kF16Max) status_raise(a.status, kFaultRange);
 }
 
+// ------------------------------------------------------------------ direct chain
+// The chain for launches of few heads, where what counts is the time of one chunk (there
+// are fewer 16-column blocks of S than the chip has SIMDs to hold them). A workgroup is
+// one 16-column block, with one wave per task:
+//   wave 0 carries S from chunk to chunk and does only what the next chunk waits for (U and
+//     the state step); it leaves f16 copies of the chunk's S and U in LDS;
+//   wave 1, a chunk behind, forms the outputs from them;
+//   wave 2, a chunk ahead, forms T_v V (fp32, through LDS: wave 0's U starts from it);
+//   wave 3 touches every line that the others will read, kAhead chunks ahead, so that their
+//     loads find it in L2 (the blocks of a head share the work).
+// The waves meet at one barrier per chunk (LDS only). All read their operands as whole
+// fragments from the workspace straight into registers, those of the next chunk while
+// this one's are used: nothing is staged. The blocks of a head run on one die and share its
+// L2. Every block reads the head's W, T_v and k^T for itself, so launches that fill the chip
+// keep the staged chain above.
+constexpr int kDirectThreads = 256;
+constexpr int kAhead = 4;
+template <int DK, int C>
+__global__ __launch_bounds__(kDirectThreads, 1) void k_delta_chain_direct(DeltaArgs a) {
+  constexpr int CC = C < 32 ? 32 : C;
+  constexpr int NRB = C / 16, NDB = DK / 16, NKD = DK / 32, NKS = CC / 32;
+  constexpr int DV = DK;
+  __shared__ __attribute__((aligned(16))) f16x8 x_s[2][NKD][64];   // -S of the chunk's start, f16 operands
+  __shared__ __attribute__((aligned(16))) f16x8 x_u[2][NKS][64];   // U, f16 operands
+  __shared__ __attribute__((aligned(16))) f32x4 x_v[2][NRB][64];   // T_v V, accumulators
+
+  const int Hv = a.n_v_heads, Hk = a.n_k_heads, G = Hv / Hk;
+  const int item = xcd_remap(blockIdx.x, gridDim.x);
+  const int si = item / (Hv * NDB);
+  if (si >= a.n_seq) return;
+  const int rem = item - si * Hv * NDB;
+  const int h = rem / NDB, kh = h / G;
+  const int i0 = (rem - h * NDB) * 16;   // first row of S (column of S^T) of the block
+  const DeltaSeq S = a.seq[si];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g4 = lane >> 4;
+  const int n = S.n_chunks;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // chunks past the last repeat it: the loads in flight stay the same
+  auto slot_of = [&](int lc) { return (long)(S.chunk_begin + min(lc, n - 1)) * Hv + h; };
+
+  if (wave == 0) {
+    float big = 0.f;   // largest magnitude this lane rounds to f16
+    u32x4 w[NRB][NKD], kt[NDB][NKS];
+    f32x4 dc[NRB];
+    float g_last;
+    auto load_w = [&](int lc) __attribute__((always_inline)) {
+      const u32x4* p = (const u32x4*)(a.ws_w + slot_of(lc) * C * DK) + lane;
+#pragma unroll
+      for (int kk = 0; kk < NKD; ++kk)
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) w[rb][kk] = p[(rb * NKD + kk) * 64];
+    };
+    auto load_dec = [&](int lc) __attribute__((always_inline)) {
+      const float* p = a.ws_dec + 2 * slot_of(lc) * C;
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) dc[rb] = *(const f32x4*)(p + 16 * rb + 4 * g4);
+      g_last = p[2 * C - 1];
+    };
+    auto load_kt = [&](int lc) __attribute__((always_inline)) {
+      const u32x4* p = (const u32x4*)(a.ws_kt + ((long)(S.chunk_begin + min(lc, n - 1)) * Hk + kh) * DK * CC) + lane;
+#pragma unroll
+      for (int kk = 0; kk < NKS; ++kk)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) kt[db][kk] = p[(db * NKS + kk) * 64];
+    };
+    // S^T rows 16 db + 4 g4 + e, column i0 + l16, and its negated f16 copy as operands
+    float* Sg = S.state + (long)h * DV * DK + (long)(i0 + l16) * DK;
+    f32x4 st[NDB];
+    f16x8 sh[NKD];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) st[db] = *(const f32x4*)(Sg + 16 * db + 4 * g4);
+    // in the loop's order, so that its waits are the same from both sides
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_dec(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_kt(0);
+    __builtin_amdgcn_sched_barrier(0);
+    auto refresh_sh = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int kk = 0; kk < NKD; ++kk) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sh[kk][e] = (_Float16)(-st[2 * kk][e]);
+          sh[kk][4 + e] = (_Float16)(-st[2 * kk + 1][e]);
+        }
+        big = fmaxf(big, fmaxf(max_abs4(st[2 * kk]), max_abs4(st[2 * kk + 1])));
+      }
+    };
+    refresh_sh();
+    lds_barrier();   // T_v V of chunk 0 is in LDS
+    for (int lc = 0; lc < n; ++lc) {
+      // U = T_v V + W (-S)^T: rows 16 rb + 4 g4 + e, column l16
+      f32x4 u[NRB];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) u[rb] = x_v[lc & 1][rb][lane];
+#pragma unroll
+      for (int kk = 0; kk < NKD; ++kk) {
+        x_s[lc & 1][kk][lane] = sh[kk];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) u[rb] = mfma_f16(__builtin_bit_cast(f16x8, w[rb][kk]), sh[kk], u[rb]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      load_w(lc + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      f16x8 uh[NKS], ud[NKS];
+#pragma unroll
+      for (int kk = 0; kk < NKS; ++kk) uh[kk] = ud[kk] = zero_f16x8();
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float uu = u[rb][e];
+          big = fmaxf(big, fabsf(uu));
+          uh[rb >> 1][4 * (rb & 1) + e] = (_Float16)uu;
+          ud[rb >> 1][4 * (rb & 1) + e] = (_Float16)(dc[rb][e] * uu);
+        }
+#pragma unroll
+      for (int kk = 0; kk < NKS; ++kk) x_u[lc & 1][kk][lane] = uh[kk];
+      // S^T <- 2^lg_last S^T + K^T (decayed U)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) st[db] = st[db] * g_last;
+      __builtin_amdgcn_sched_barrier(0);
+      load_dec(lc + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < NKS; ++kk)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) st[db] = mfma_f16(__builtin_bit_cast(f16x8, kt[db][kk]), ud[kk], st[db]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_kt(lc + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      refresh_sh();
+      lds_barrier();   // S and U of chunk lc and T_v V of lc + 1 are in LDS; those before have been read
+    }
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) *(f32x4*)(Sg + 16 * db + 4 * g4) = st[db];
+    if (big > kF16Max) status_raise(a.status, kFaultRange);
+  } else if (wave == 1) {
+    u32x4 q[NRB][NKD], pp[NRB][NKS];
+    float dg[NRB];
+    auto load_qp = [&](int lc) __attribute__((always_inline)) {
+      const long c = S.chunk_begin + min(lc, n - 1);
+      const u32x4* qp = (const u32x4*)(a.ws_q + (c * Hk + kh) * C * DK) + lane;
+      const u32x4* pf = (const u32x4*)(a.ws_p + (c * Hv + h) * C * CC) + lane;
+      const float* d = a.ws_dec + (2 * (c * Hv + h) + 1) * C + l16;
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) {
+#pragma unroll
+        for (int kk = 0; kk < NKD; ++kk) q[rb][kk] = qp[(rb * NKD + kk) * 64];
+#pragma unroll
+        for (int kk = 0; kk < NKS; ++kk) pp[rb][kk] = pf[(rb * NKS + kk) * 64];
+        dg[rb] = d[16 * rb];
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    load_qp(0);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    for (int lc = 0; lc < n; ++lc) {
+      lds_barrier();   // chunk lc's S and U are in LDS
+      f16x8 sh[NKD], uh[NKS];
+#pragma unroll
+      for (int kk = 0; kk < NKD; ++kk) sh[kk] = x_s[lc & 1][kk][lane];
+#pragma unroll
+      for (int kk = 0; kk < NKS; ++kk) uh[kk] = x_u[lc & 1][kk][lane];
+      // O^T = scale 2^lg S Q^T + U^T P^T: rows i0 + 4 g4 + e, column (token) 16 rb + l16
+      f32x4 y[NRB];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) {
+        y[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < NKD; ++kk) y[rb] = mfma_f16(sh[kk], __builtin_bit_cast(f16x8, q[rb][kk]), y[rb]);
+      }
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) {
+        y[rb] = y[rb] * (-a.scale * dg[rb]);
+#pragma unroll
+        for (int kk = 0; kk < NKS; ++kk) y[rb] = mfma_f16(uh[kk], __builtin_bit_cast(f16x8, pp[rb][kk]), y[rb]);
+      }
+      const int t0 = lc * C;
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+        if (t0 + 16 * rb + l16 < S.T)
+          *(f32x4*)(S.out + ((long)(t0 + 16 * rb + l16) * Hv + h) * DV + i0 + 4 * g4) = y[rb];
+      __builtin_amdgcn_sched_barrier(0);
+      load_qp(lc + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else if (wave == 2) {
+    float big = 0.f;
+    u32x4 tv[NRB][NKS];
+    uint16_t vr[NKS][8];
+    auto load_tv = [&](int lc) __attribute__((always_inline)) {
+      const u32x4* p = (const u32x4*)(a.ws_tv + slot_of(lc) * C * CC) + lane;
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int kk = 0; kk < NKS; ++kk) tv[rb][kk] = p[(rb * NKS + kk) * 64];
+      // v of tokens 32 kk + 8 g4 .. + 7, column l16; past the tail its last token (times the
+      // zero columns of T_v)
+      const int t0 = min(lc, n - 1) * C;
+      const bf16_t* v = S.v + ((long)t0 * Hv + h) * DV + i0;
+      const int vrow = Hv * DV;
+      if (t0 + CC <= S.T) {
+        const int at = 8 * g4 * vrow + l16;
+#pragma unroll
+        for (int kk = 0; kk < NKS; ++kk)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) vr[kk][j] = (v + (32 * kk + j) * vrow)[at];
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < NKS; ++kk)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) vr[kk][j] = v[min(32 * kk + 8 * g4 + j, S.T - 1 - t0) * vrow + l16];
+      }
+    };
+    auto form = [&](int lc) __attribute__((always_inline)) {
+      f32x4 u[NRB];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) u[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < NKS; ++kk) {
+        f16x8 vh;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float x = C >= 32 || g4 < 2 ? bf16_to_f32(vr[kk][j]) : 0.f;
+          big = fmaxf(big, fabsf(x));
+          vh[j] = (_Float16)x;
+        }
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) u[rb] = mfma_f16(__builtin_bit_cast(f16x8, tv[rb][kk]), vh, u[rb]);
+      }
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) x_v[lc & 1][rb][lane] = u[rb];
+    };
+    load_tv(0);
+    form(0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_tv(1);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    for (int lc = 0; lc < n; ++lc) {
+      form(lc + 1);   // past the last chunk: the last one again, read by no one
+      __builtin_amdgcn_sched_barrier(0);
+      load_tv(lc + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      lds_barrier();
+    }
+    if (big > kF16Max) status_raise(a.status, kFaultRange);
+  } else {
+    // one word of every line of a chunk's operands and v rows, kAhead chunks ahead: the
+    // head's NDB blocks share them out
+    constexpr int kW = C * DK / 64, kT = C * CC / 64, kK = DK * CC / 64, kV = C * DK / 64;   // lines (64 f16)
+    constexpr int kLines = 2 * kW + 2 * kT + kK + kV;
+    constexpr int NP = (kLines + NDB * 64 - 1) / (NDB * 64);
+    const int first = (i0 / 16) * 64 + lane;
+    auto request = [&](uint32_t (&x)[NP], int lc) __attribute__((always_inline)) {
+      const long c = S.chunk_begin + min(lc, n - 1);
+      const long sv = c * Hv + h, sk = c * Hk + kh;
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        int e = first + j * NDB * 64;
+        const void* p = a.ws_w + sv * C * DK + min(e, kW - 1) * 64;
+        if ((e -= kW) >= 0) p = a.ws_q + sk * C * DK + min(e, kW - 1) * 64;
+        if ((e -= kW) >= 0) p = a.ws_kt + sk * DK * CC + min(e, kK - 1) * 64;
+        if ((e -= kK) >= 0) p = a.ws_tv + sv * C * CC + min(e, kT - 1) * 64;
+        if ((e -= kT) >= 0) p = a.ws_p + sv * C * CC + min(e, kT - 1) * 64;
+        if ((e -= kT) >= 0) {
+          const int r = min(e, kV - 1) / (DK / 64), q = min(e, kV - 1) % (DK / 64);
+          p = S.v + ((long)min(min(lc, n - 1) * C + r, S.T - 1) * Hv + h) * DV + q * 64;
+        }
+        x[j] = *(const uint32_t*)p;
+      }
+    };
+    // a request's words are only taken (and dropped) kRing chunks later
+    constexpr int kRing = 4;
+    uint32_t ring[kRing][NP];
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) request(ring[k], min(k + 1, kAhead - 1));
+    lds_barrier();
+    for (int lc = 0; lc < n; lc += kRing) {
+#pragma unroll
+      for (int k = 0; k < kRing; ++k) {
+        if (lc + k >= n) break;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) asm volatile("" ::"v"(ring[k][j]));
+        request(ring[k], lc + k + kAhead);
+        lds_barrier();
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kRing; ++k)
+#pragma unroll
+      for (int j = 0; j < NP; ++j) asm volatile("" ::"v"(ring[k][j]));
+  }
+}
+
 static_assert(sizeof(DeltaArgs) <= kMaxKernargBytes, "delta launch record");
 
 template <int DK, int C>
@@ -702,6 +1017,11 @@ hipError_t prep_for(const DeltaArgs& a, hipStream_t s) {
 
 template <int DK, int C>
 hipError_t chain_for(const DeltaArgs& a, hipStream_t s) {
+  if (a.n_slices == DK / 16 && a.direct) {
+    const int blocks = (a.n_seq * a.n_v_heads * (DK / 16) + 7) & ~7;
+    hipLaunchKernelGGL((k_delta_chain_direct<DK, C>), dim3(blocks), dim3(kDirectThreads), 0, s, a);
+    return hipGetLastError();
+  }
   const int blocks = (a.n_seq * a.n_v_heads * a.n_slices + 7) & ~7;   // xcd_remap wants a multiple of 8
   const int dvs = DK / a.n_slices;
   if (dvs == 16)

@@ -1,0 +1,66 @@
+"""GPU tests of both delta-rule chains against the float64 oracle (MI355X only).
+
+Launches of at most 256 blocks of 16 state columns (items x value heads x d / 16) take the
+direct chain, larger ones the staged one: every head size and chunk length on both sides
+of the limit, whole and ragged chunks, one chunk, and the same results from both.
+"""
+import pytest
+import torch
+
+import synth
+import paper_2609_18935_amd as tu
+from gpu_cases import DEV, DeltaCase, assert_close, delta_oracle_heads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    tu.lib()
+
+
+def _params(s):
+    return tu.delta_params(s.n_k_heads, s.n_v_heads, s.d_k, s.d_v, s.chunk, s.scale)
+
+
+@pytest.mark.parametrize("d,hv", [(128, 32), (128, 34), (64, 64), (64, 66)])   # 256 blocks, and a few more
+@pytest.mark.parametrize("chunk", [16, 32, 64])
+@pytest.mark.parametrize("T", [33, 64, 127])
+def test_chains_match_oracle(d, hv, chunk, T):
+    print(f"[case] delta chain hv={hv} d={d} chunk={chunk} T={T}", flush=True)
+    s = synth.DeltaShape(hv // 2, hv, d, d, chunk)
+    c = DeltaCase(s, 41, 0, 0, T)
+    ws = tu.delta_rule_continue(c.state, c.q, c.k, c.v, c.beta_d, c.g_d, _params(s), c.out)
+    torch.cuda.synchronize()
+    assert tu.workspace_faults(ws) == 0
+    vh, o, S = delta_oracle_heads(c.S0, c.q_b, c.k_b, c.v_b, c.beta, c.g, s.scale, [0, hv // 4, hv // 2 - 1])
+    assert_close(c.out.cpu().numpy()[:, vh], o, "out")
+    assert_close(c.state.cpu().numpy()[vh], S, "state")
+
+
+@pytest.mark.parametrize("chunk", [16, 64])
+def test_direct_chain_over_many_chunks_and_contexts(chunk):
+    """Three contexts of different lengths (one of a single chunk) in one direct launch: each
+    matches the oracle and equals its own call, where that takes the chunked form as well (a
+    tail of at most 32 tokens on its own goes token by token)."""
+    s = synth.DeltaShape(2, 4, 128, 128, chunk)
+    tails = (700, chunk, 1025)
+    print(f"[case] direct chain, chunk {chunk}, tails {tails}", flush=True)
+    cases = [DeltaCase(s, 42, 0, 0, T, char=i) for i, T in enumerate(tails)]
+    out = torch.full((sum(tails), 4, 128), float("nan"), device=DEV)
+    states = [c.state.clone() for c in cases]
+    cat = lambda name: torch.cat([getattr(c, name) for c in cases])  # noqa: E731
+    layer = tu.LayerIO(tu.TU_LAYER_DELTA, cat("q"), cat("k"), cat("v"), out, state=states, beta=cat("beta_d"),
+                       g=cat("g_d"))
+    tu.update_layer_stack([tu.Context(2048, device=DEV) for _ in tails], [[]] * 3, list(tails), [layer],
+                          tu.attn_params(2, 1, 64), _params(s))
+    at = 0
+    for c, st, T in zip(cases, states, tails):
+        tu.delta_rule_continue(c.state, c.q, c.k, c.v, c.beta_d, c.g_d, _params(s), c.out)
+        assert T <= 32 or (torch.equal(c.out, out[at:at + T]) and torch.equal(c.state, st))
+        o, S = c.oracle()
+        assert_close(out[at:at + T].cpu().numpy(), o, f"T={T} out")
+        assert_close(st.cpu().numpy(), S, f"T={T} state")
+        at += T
