@@ -189,8 +189,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
   }
   lds_barrier();
 
-  // ---- phase 1: cumulative log-decay (wave 0) and K K^T, Q K^T lower blocks (MFMA)
-  if (wave == 0) {
+  // ---- phase 1: cumulative log-decay (the last wave: it has the fewest blocks below) and
+  // K K^T, Q K^T lower blocks (MFMA)
+  if (wave == NW - 1) {
     float x = lane < C ? lg[lane] : 0.f;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -282,17 +283,19 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
       *(f16x8*)&Qg[frag_at<NKD>(r, 8 * v8)] = hq;
     }
   }
-  // zero the upper blocks of P and the padding of its rows
-  for (int e = tid; e < C * CC / 4; e += NT) {
-    const int r = e / (CC / 4), i = (e - r * (CC / 4)) * 4;
-    if (i >= C || (i >> 4) > (r >> 4)) *(uint2*)&Pg[frag_at<NKS>(r, perm32(i))] = uint2{0, 0};
-  }
-  // the chain's decay factors: to the chunk's end, and from its start
-  if (tid < C) {
-    a.ws_dec[(2 * slot) * C + tid] = __builtin_amdgcn_exp2f(lg[C - 1] - lg[tid]);
-    a.ws_dec[(2 * slot + 1) * C + tid] = __builtin_amdgcn_exp2f(lg[tid]);
-  }
   lds_barrier();
+
+  // the k rows of phase 5's k^T, read again (from L2: phase 0 read them) and requested here,
+  // two phases before they are used
+  constexpr int NKI = ((C / 2) * (DK / 8) + NT - 1) / NT;
+  u32x4 kr[NKI][2];
+#pragma unroll
+  for (int p = 0; p < NKI; ++p) {
+    const int e = min(tid + p * NT, (C / 2) * (DK / 8) - 1);
+    const int s2 = (e % (C / 2)) * 2, d0 = (e / (C / 2)) * 8;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) kr[p][q] = *(const u32x4*)(S.k + ((long)(t0 + min(s2 + q, Cr - 1)) * Hk + kh) * DK + d0);
+  }
 
   // ---- phase 3: diagonal 16x16 blocks of T = (I + M)^-1, one lane per column: forward
   // substitution, with the next row of M read while the current one is summed
@@ -320,6 +323,19 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
     }
 #pragma unroll
     for (int rr = 0; rr < 16; ++rr) Tt[tri(16 * b + rr, 16 * b + cc)] = x[rr];
+  }
+  if (wave > 0) {   // the other waves meanwhile:
+    // zero the upper blocks of P and the padding of its rows
+    for (int e = tid - 64; e < C * CC / 4; e += NT - 64) {
+      const int r = e / (CC / 4), i = (e - r * (CC / 4)) * 4;
+      if (i >= C || (i >> 4) > (r >> 4)) *(uint2*)&Pg[frag_at<NKS>(r, perm32(i))] = uint2{0, 0};
+    }
+    // the chain's decay factors: to the chunk's end, and from its start
+    const int t = tid - 64;
+    if (t < C) {
+      a.ws_dec[(2 * slot) * C + t] = __builtin_amdgcn_exp2f(lg[C - 1] - lg[t]);
+      a.ws_dec[(2 * slot + 1) * C + t] = __builtin_amdgcn_exp2f(lg[t]);
+    }
   }
   lds_barrier();
 
@@ -374,12 +390,15 @@ __global__ __launch_bounds__(kPrepThreads) void k_delta_prep(DeltaArgs a) {
     *(f16x4*)&Twh[r][i0] = hw;
     *(f16x4*)&Tvg[frag_at<NKS>(r, i0)] = hv;
   }
-  // k^T in f16 over the dead M, from the k rows read again (from L2: phase 0 read them)
-  for (int e = tid; e < (C / 2) * (DK / 8); e += NT) {
+  // k^T in f16 over the dead M
+#pragma unroll
+  for (int p = 0; p < NKI; ++p) {
+    const int e = tid + p * NT;
+    if ((C / 2) * (DK / 8) % NT != 0 && e >= (C / 2) * (DK / 8)) break;
     const int s2 = (e % (C / 2)) * 2, d0 = (e / (C / 2)) * 8;
     const u32x4 z4 = {0, 0, 0, 0};
-    const u32x4 k0 = s2 < Cr ? *(const u32x4*)(S.k + ((long)(t0 + s2) * Hk + kh) * DK + d0) : z4;
-    const u32x4 k1 = s2 + 1 < Cr ? *(const u32x4*)(S.k + ((long)(t0 + s2 + 1) * Hk + kh) * DK + d0) : z4;
+    const u32x4 k0 = s2 < Cr ? kr[p][0] : z4;
+    const u32x4 k1 = s2 + 1 < Cr ? kr[p][1] : z4;
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
       const uint32_t b0 = (d & 1) ? (k0[d >> 1] & 0xFFFF0000u) : (k0[d >> 1] << 16);
