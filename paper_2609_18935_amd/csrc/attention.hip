@@ -352,9 +352,24 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (kt_begin < kt_end) {
     load_k(IntC<0>{}, kt_begin);
     load_v(IntC<0>{}, kt_begin);
-    for (int kt = kt_begin; kt < kt_end; kt += 2) {
-      step(IntC<0>{}, kt);
-      if (kt + 1 < kt_end) step(IntC<1>{}, kt + 1);
+    // a wave without rows (in the last query tile of a context) only loads and meets the
+    // others: a loop of its own, since a branch in the loop below lengthens every unit
+    if (__builtin_expect(tile * kBM + wave * 32 < rows_total, 1)) {
+      for (int kt = kt_begin; kt < kt_end; kt += 2) {
+        step(IntC<0>{}, kt);
+        if (kt + 1 < kt_end) step(IntC<1>{}, kt + 1);
+      }
+    } else {
+      auto pass = [&](auto bc, int kt) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(vm_wait(0));
+        wg_barrier();
+        load_k(bc, kt + 1);
+        load_v(bc, kt + 1);
+      };
+      for (int kt = kt_begin; kt < kt_end; kt += 2) {
+        pass(IntC<1>{}, kt);
+        if (kt + 1 < kt_end) pass(IntC<0>{}, kt + 1);
+      }
     }
     __builtin_amdgcn_s_waitcnt(vm_wait(0));  // no tile write may outlive the workgroup
   }
