@@ -53,9 +53,9 @@ def _resources(remarks: str) -> dict:
 # Per-file options: MFMA accumulators in ordinary vector registers. The attention kernel runs
 # two waves per SIMD (256 registers each) and may then use the whole budget, instead of
 # splitting it in equal accumulator and vector halves; the delta rule's direct chain is
-# spared 90 register moves per chunk.
+# spared 90 register moves per chunk, the probe's score passes one per score.
 _VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]
-FILE_FLAGS = {"attention.hip": _VGPR_MFMA, "delta.hip": _VGPR_MFMA}
+FILE_FLAGS = {"attention.hip": _VGPR_MFMA, "delta.hip": _VGPR_MFMA, "probe.hip": _VGPR_MFMA}
 
 
 def _compile(src: str):
