@@ -243,7 +243,7 @@ int refresh_vt_cache(tu_seq* seq, void* const* v_layers, void* const* vt_layers,
  *  q_hat: optional device bf16 [T][n_q_heads][head_dim] receiving the rotated queries.
  *  vt_cache: optional V^T copy of this layer (tu_vt_cache_bytes(seq->capacity, ...));
  *     tiles from row seq->vt_rows on are refreshed. NULL: every tile is packed into the
- *     workspace.
+ *     workspace, or none where the tail is short enough to read V as it lies in the cache.
  * Does not change `seq` (several layers share one context): call commit_tail once
  * after the last layer, or use update_layer_stack.
  */
@@ -263,7 +263,8 @@ int commit_tail(tu_seq* seq, int64_t T);
  * state, for each tail token t
  *   S <- g_t * S (I - beta_t k_t k_t^T) + beta_t v_t k_t^T,   o_t = scale * S q_t,
  * evaluated in chunks of p->chunk tokens (chunk-parallel WY preparation, then a
- * sequential chain over chunks with the fp32 state held on chip).
+ * sequential chain over chunks with the fp32 state held on chip); tails of a few tokens
+ * (at most 32) are evaluated token by token in fp32.
  *  state: device fp32 [n_v_heads][d_v][d_k], updated in place.
  *  q, k:  device bf16 [T][n_k_heads][d_k];  v: device bf16 [T][n_v_heads][d_v].
  *  beta, g: device fp32 [T][n_v_heads];  out: device fp32 [T][n_v_heads][d_v].
