@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     load_v(IntC<0>{}, kt_begin);
     // a wave without rows (in the last query tile of a context) only loads and meets the
     // others: a loop of its own, since a branch in the loop below lengthens every unit
-    if (__builtin_expect(tile * kBM + wave * 32 < rows_total, 1)) {
+    if (tile * kBM + wave * 32 < rows_total) {
       for (int kt = kt_begin; kt < kt_end; kt += 2) {
         step(IntC<0>{}, kt);
         if (kt + 1 < kt_end) step(IntC<1>{}, kt + 1);
