@@ -704,7 +704,8 @@ def sources_sha256(srcs):
 
 # sources each kernel's traffic record depends on
 KERNEL_SOURCES = {
-    "attention": ["paper_2609_18935_amd/csrc/attention.hip", "paper_2609_18935_amd/csrc/common.h"],
+    "attention": ["paper_2609_18935_amd/csrc/attention.hip", "paper_2609_18935_amd/csrc/attention_tile.h",
+                  "paper_2609_18935_amd/csrc/common.h"],
 }
 KERNEL_SYMBOL = {"attention": "k_attn<256>"}
 
