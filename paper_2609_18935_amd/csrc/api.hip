@@ -852,8 +852,18 @@ int64_t step_tokens(int64_t heads) { return heads <= kCus / 2 ? kStepTokens : kS
 // eight layers take 205 / 466 us.
 constexpr int64_t kDirectBlocks = kCus;
 
+// Cache rows, over the layers and contexts of the attention that runs beside a delta launch,
+// up to which that launch takes the direct chain. It ends sooner than the staged chain but
+// holds twice the CUs, more CU time in all: an attention that fills the chip for longer than
+// the chain pays for it. Update of one attention and one delta layer (staged / direct): 1,072
+// tokens over 5,751 rows 178.3 / 174.0 us, 870 over 6,934 rows 172.6 / 166.2 us, 564 over
+// 11,472 rows 174.8 / 174.7 us, 637 over 37,031 rows 421.4 / 424.3 us, 303 over 40,235 rows
+// 243.0 / 244.1 us, 861 over 63,046 rows 897 / 903 us.
+constexpr int64_t kDirectRows = 12288;
+
+// `beside_rows`: cache rows of the attention layers that run beside these items
 int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, void* ws, const CallStatus& status,
-               std::vector<DeltaArgs>* out, size_t* ws_bytes) {
+               std::vector<DeltaArgs>* out, size_t* ws_bytes, int64_t beside_rows = 0) {
   const int C = p->chunk, Hv = p->n_v_heads, DK = p->d_k;
   size_t max_used = 0;
   out->clear();
@@ -870,7 +880,7 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
     a.n_k_heads = p->n_k_heads;
     a.n_v_heads = Hv;
     a.scale = p->scale;
-    a.direct = (int64_t)n_active * Hv * (DK / 16) <= kDirectBlocks;
+    a.direct = (int64_t)n_active * Hv * (DK / 16) <= kDirectBlocks && beside_rows <= kDirectRows;
     a.n_slices = a.direct ? DK / 16 : DK / dvs;
     a.status = status;
     int64_t longest = 0;
@@ -1641,7 +1651,7 @@ StackWorkspace stack_workspace(const tu_update* u, StackPlan& sp) {
   auto items = stack_delta_items(u, sp);
   if (!items.empty()) {
     std::vector<DeltaArgs> ls;
-    plan_delta(&u->delta, items, nullptr, CallStatus{}, &ls, &w.delta);
+    plan_delta(&u->delta, items, nullptr, CallStatus{}, &ls, &w.delta);   // the same bytes for either chain
   }
   return w;
 }
@@ -1931,7 +1941,10 @@ int update_layer_stack(const tu_update* u, void* workspace, size_t workspace_byt
       size_t b = 0;
       auto items = stack_delta_items(u, sp);
       std::vector<DeltaArgs> ls;
-      plan_delta(&u->delta, items, ws_delta, status, &ls, &b);
+      int64_t rows = 0;
+      for (int s = 0; s < u->n_seq; ++s)
+        if (u->seqs[s].T > 0) rows += sp.n_attn * (u->seqs[s].seq->len + u->seqs[s].T);
+      plan_delta(&u->delta, items, ws_delta, status, &ls, &b, rows);
       if (int e = run_delta(ls, &u->delta, sd)) return e;
       if (side)
         if (int e = hip_check(hipEventRecord(side->join, side->stream), "join event")) return e;

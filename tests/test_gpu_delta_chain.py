@@ -1,15 +1,16 @@
 """GPU tests of both delta-rule chains against the float64 oracle (MI355X only).
 
 Launches of at most 256 blocks of 16 state columns (items x value heads x d / 16) take the
-direct chain, larger ones the staged one: every head size and chunk length on both sides
-of the limit, whole and ragged chunks, one chunk, and the same results from both.
+direct chain, larger ones and those beside attention over more than 12,288 cache rows the
+staged one: every head size and chunk length on both sides of the limits, whole and ragged
+chunks, one chunk.
 """
 import pytest
 import torch
 
 import synth
 import paper_2609_18935_amd as tu
-from gpu_cases import DEV, DeltaCase, assert_close, delta_oracle_heads
+from gpu_cases import DEV, AttnCase, DeltaCase, assert_close, delta_oracle_heads
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +65,23 @@ def test_direct_chain_over_many_chunks_and_contexts(chunk):
         assert_close(out[at:at + T].cpu().numpy(), o, f"T={T} out")
         assert_close(st.cpu().numpy(), S, f"T={T} state")
         at += T
+
+
+@pytest.mark.parametrize("layers", [1, 2])
+@pytest.mark.parametrize("over", [0, 1])
+def test_chains_beside_attention_match_oracle(layers, over):
+    """Attention layers over exactly 12,288 cache rows, and over one row more each."""
+    T, rows = 100, 12288 // layers + over
+    print(f"[case] delta chain beside {layers} attention layers of {rows} rows", flush=True)
+    a, s = synth.AttnShape(2, 1, 64), synth.DeltaShape(2, 4, 128, 128, 32)
+    acs = [AttnCase(a, 43, 0, i, rows - T, T) for i in range(layers)]
+    c = DeltaCase(s, 43, 0, layers, T)
+    ctx = tu.Context(rows, device=DEV)
+    ctx.pos[:rows - T] = torch.arange(rows - T, dtype=torch.int32, device=DEV)
+    ctx.set_metadata([(0, rows - T)], rows - T)
+    io = [tu.LayerIO(tu.TU_LAYER_ATTN, x.q, x.k, x.v, x.out, k_cache=[x.k_cache], v_cache=[x.v_cache]) for x in acs]
+    io.append(tu.LayerIO(tu.TU_LAYER_DELTA, c.q, c.k, c.v, c.out, state=[c.state], beta=c.beta_d, g=c.g_d))
+    tu.update_layer_stack([ctx], [[]], [T], io, tu.attn_params(2, 1, 64, a.rdim, a.rope_theta), _params(s))
+    o, S = c.oracle()
+    assert_close(c.out.cpu().numpy(), o, "out")
+    assert_close(c.state.cpu().numpy(), S, "state")
