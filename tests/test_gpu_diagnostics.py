@@ -88,6 +88,33 @@ def test_probe_distribution_two_layers(placement):
     _close(got, p_ref, f"probe distribution ({placement})")
 
 
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_probe_scores_of_minus_infinity(D):
+    """Visible keys whose score is -inf (an infinite key component, an overflowed dot
+    product) or finite and below -2.4e38 have probability 0 and leave the other rows'
+    distribution as it is, in 32-key blocks that every row sees whole and in the last one."""
+    L, n, hq, hkv = 333, 4, 4, 2
+    _say(f"probe scores of -inf and -3e38, D={D}")
+    rng = np.random.default_rng(60 + D)
+    k, q = (rng.normal(0.0, D ** -0.25, s) for s in ((L, hkv, D), (n, hq, D)))
+    q[:, :, D - 2:] = 1.0                      # past the rotary dims: the score takes these as they are
+    hidden = {5: (0.0, -np.inf), 70: (0.0, -3.0e38), 71: (-3.0e38, -3.0e38), 200: (0.0, -1000.0),
+              L - n: (0.0, -np.inf), L - n - 1: (-3.0e38, -3.0e38)}
+    for row, kv in hidden.items():
+        k[row, :, D - 2:] = kv
+    k, q, pos = synth.to_bf16_bits(k), synth.to_bf16_bits(q), np.arange(L)
+    ctx = tu.Context(L, device=DEV)
+    ctx.pos[:L] = torch.arange(L, dtype=torch.int32, device=DEV)
+    ctx.set_metadata([(0, L)], L)
+    p = tu.attn_params(hq, hkv, D, D // 2, 1.0e6, 1.0)
+    got = torch.zeros(L, dtype=torch.float32, device=DEV)
+    tu.attention_probe(ctx, to_dev_bf16(k), p, to_dev_bf16(q), got)
+    want = oracle.probe_distribution(q, pos[-n:], k, D // 2, 1.0e6, 1.0, dtype=np.float64)
+    got = got.cpu().numpy().astype(np.float64)
+    assert np.all(np.isfinite(got)) and np.all(got[list(hidden)] == 0.0) and np.all(want[list(hidden)] == 0.0)
+    _close(got, want, "probe distribution")
+
+
 @pytest.mark.parametrize("hq,hkv,d,rdim,n,L", [
     (8, 4, 128, 64, 5, 1000),     # 10 rows per KV head: one ragged row tile
     (16, 1, 64, 64, 8, 333),      # 128 rows: four row tiles, two tasks per wave
