@@ -515,40 +515,79 @@ TileSpan tile_span(int64_t L_keep, int64_t T, int G) {
 constexpr int kMaxAutoSplits = 128;
 constexpr int kGateWaves = 4;   // attention launches this many CU-waves long wait for the delta layers
 
-int choose_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t base_items_total, bool uniform) {
-  if (p->kv_splits > 0) return p->kv_splits;
-  const int64_t n_kt = (L_keep + T + kAttnKeys - 1) / kAttnKeys;
-  const int64_t max_s = std::max<int64_t>(1, std::min<int64_t>(kMaxAutoSplits, n_kt / 4));
-  if (!uniform) {
-    const int64_t want = std::max<int64_t>(1, (kCus + base_items_total - 1) / std::max<int64_t>(1, base_items_total));
-    return (int)std::min(want, max_s);
+// Estimated time of a launch of equal items (see above) with its key range in s parts.
+// `lo`: key tiles of its shortest query tile. With fp32 partial outputs these take twice the
+// bytes, and a key tile at least the 1.3 us that one of head_dim 64 takes (measured, 2,100 to
+// 9,000 keys; the f16 estimate keeps the price in proportion to head_dim that its choices
+// were measured with).
+double split_time(const tu_attn_params* p, const TileSpan& span, int64_t T, int64_t base_items, int64_t s, bool f32) {
+  const double tile_us = std::max(3.8 * p->head_dim / 256.0, f32 ? 1.3 : 0.0);
+  const double wave_us = 4.0 + 8.0 * p->head_dim / 256.0;
+  const double split_us = (double)T * p->n_q_heads * p->head_dim * (f32 ? 8.0 : 4.0) / 5e6;
+  const int64_t waves = (base_items * s + kCus - 1) / kCus;
+  const int64_t longest = (span.hi + s - 1) / s, shortest = (span.lo + s - 1) / s;
+  // lengths fall evenly from longest to shortest; paired waves fill each other's gaps
+  double tiles = (double)longest;
+  if (waves > 1) {
+    const auto at = [&](int64_t wave) {
+      return (double)longest - (double)(longest - shortest) * (double)(wave * kCus) / (double)(base_items * s);
+    };
+    double sum = waves & 1 ? at(waves - 1) : 0.0;
+    for (int64_t w = 1; w < waves; w += 2) sum += 2.0 * at(w);
+    tiles = std::max(tiles, sum);
   }
-  const double tile_us = 3.8 * p->head_dim / 256.0, wave_us = 4.0 + 8.0 * p->head_dim / 256.0;
-  const double split_us = (double)T * p->n_q_heads * p->head_dim * 4.0 / 5e6;
+  const double est = tiles * tile_us + waves * wave_us + (s > 1 ? 8.0 + split_us * s : 0.0);
+  return waves > 1 && longest > shortest ? 1.03 * est : est;   // uneven items never pack quite as well
+}
+
+int64_t max_splits(int64_t L_keep, int64_t T) {
+  return std::max<int64_t>(1, std::min<int64_t>(kMaxAutoSplits, (L_keep + T + kAttnKeys - 1) / kAttnKeys / 4));
+}
+
+// Split count of one context, and whether its partial outputs are fp32.
+struct Splits {
+  int n;
+  bool f32;
+};
+
+// Whether the long kernel would run a context's key range whole if its query tiles were of
+// equal length. Splits are there to fill the chip, and their partial outputs are f16; a
+// launch that fills it as it is, or is too short to gain, is split only because its tiles are
+// uneven or because the short kernel's units are smaller. Its results need not pass through
+// f16: it writes fp32 partials (16/2 heads of 256, no context, 4,096 tokens in 2 splits:
+// error against 64 bits 2.69e-4 with f16 partials, 1.78e-4 with fp32, 1.81e-4 whole; 206 us,
+// whole 239 us). Elsewhere fp32 would cost more than it gives: one token over 32,768 rows
+// 27.3 -> 28.5 us.
+bool runs_whole(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t base_items, bool uniform) {
+  const int64_t max_s = max_splits(L_keep, T);
+  if (!uniform) return max_s == 1 || base_items >= kCus;
+  TileSpan span = tile_span(L_keep, T, p->n_q_heads / p->n_kv_heads);
+  span.lo = span.hi;
+  const double whole = split_time(p, span, T, base_items, 1, false);
+  for (int64_t s = 2; s <= max_s; ++s)
+    if (split_time(p, span, T, base_items, s, false) < whole) return false;
+  return true;
+}
+
+Splits choose_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t base_items, bool uniform) {
+  if (p->kv_splits > 0) return {p->kv_splits, false};
+  const int64_t max_s = max_splits(L_keep, T);
+  if (!uniform) {
+    const int64_t want = std::max<int64_t>(1, (kCus + base_items - 1) / std::max<int64_t>(1, base_items));
+    return {(int)std::min(want, max_s), false};
+  }
+  const bool f32 = runs_whole(p, L_keep, T, base_items, uniform);
   const TileSpan span = tile_span(L_keep, T, p->n_q_heads / p->n_kv_heads);
   double best = 0.0;
   int best_s = 1;
   for (int64_t s = 1; s <= max_s; ++s) {
-    const int64_t waves = (base_items_total * s + kCus - 1) / kCus;
-    const int64_t longest = (span.hi + s - 1) / s, shortest = (span.lo + s - 1) / s;
-    // lengths fall evenly from longest to shortest; paired waves fill each other's gaps
-    double tiles = (double)longest;
-    if (waves > 1) {
-      const auto at = [&](int64_t wave) {
-        return (double)longest - (double)(longest - shortest) * (double)(wave * kCus) / (double)(base_items_total * s);
-      };
-      double sum = waves & 1 ? at(waves - 1) : 0.0;
-      for (int64_t w = 1; w < waves; w += 2) sum += 2.0 * at(w);
-      tiles = std::max(tiles, sum);
-    }
-    double est = tiles * tile_us + waves * wave_us + (s > 1 ? 8.0 + split_us * s : 0.0);
-    if (waves > 1 && longest > shortest) est *= 1.03;   // uneven items never pack quite as well
+    const double est = split_time(p, span, T, base_items, s, f32);
     if (s == 1 || est < best) {
       best = est;
       best_s = (int)s;
     }
   }
-  return best_s;
+  return {best_s, f32};
 }
 
 // Die table of a launch of several contexts: groups (context, kv head, split) cost their
@@ -636,13 +675,15 @@ constexpr int64_t kShortWork = 8192;
 // reads an equal share of the launch's units (`work`); a workgroup's four waves take at
 // least one unit each. A context of up to two units per wave (four of shorter rows) is not
 // split: the merge launch would take longer.
-int short_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t work) {
-  if (p->kv_splits > 0) return p->kv_splits;
+Splits short_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t work, int64_t base_items,
+                    bool uniform) {
+  if (p->kv_splits > 0) return {p->kv_splits, false};
   const int64_t units = (L_keep + T + kShortKeys - 1) / kShortKeys;
   const int64_t per_wave = (units + 3) / 4;
-  if (per_wave <= (p->head_dim == 256 ? 2 : 4)) return 1;
+  if (per_wave <= (p->head_dim == 256 ? 2 : 4)) return {1, false};
   const int64_t share = units * kCus / std::max<int64_t>(1, work);
-  return (int)std::max<int64_t>(1, std::min({share, per_wave, (int64_t)kMaxAutoSplits}));
+  return {(int)std::max<int64_t>(1, std::min({share, per_wave, (int64_t)kMaxAutoSplits})),
+          runs_whole(p, L_keep, T, base_items, uniform)};
 }
 
 int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* ws, const CallStatus& status,
@@ -685,6 +726,7 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
     L.attn.scale_log2 = p->softmax_scale * 1.4426950408889634f;
     L.merge.n_q_heads = Hq;
     int tok = 0, item_total = 0, pack_total = 0, mrows = 0, n_runs = 0;
+    Splits sp{};   // the same for every context of a uniform launch
     for (size_t i = g0; i < g1; ++i) {
       const AttnItem& it = items[i];
       if (it.T <= 0) continue;
@@ -693,8 +735,10 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       if (!qh) qh = static_cast<bf16_t*>(qh_ws);
       const int tile_rows = L.short_tail ? kShortRows : kAttnRows;
       const int tiles = (int)((it.T * G + tile_rows - 1) / tile_rows);
-      const int splits = L.short_tail ? short_splits(p, it.L_keep, it.T, short_work)
-                                      : choose_splits(p, it.L_keep, it.T, base_items, uniform);
+      if (!uniform || &it == first)
+        sp = L.short_tail ? short_splits(p, it.L_keep, it.T, short_work, base_items, uniform)
+                          : choose_splits(p, it.L_keep, it.T, base_items, uniform);
+      const int splits = sp.n;
       // V^T tiles: refreshed in the layer's own copy from the first row it lacks, or all
       // packed into the workspace (the short-tail kernel reads none: nothing is packed)
       int vt_end = (int)vt_head_tiles(it.L_keep + it.T);
@@ -710,10 +754,10 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
         vt = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)Hkv * vt_end * D * kVtRow));
         head_tiles = vt_end;
       }
-      _Float16* po = nullptr;
+      void* po = nullptr;
       float* pml = nullptr;
       if (splits > 1) {
-        po = static_cast<_Float16*>(ar.take(sizeof(_Float16) * splits * it.T * Hq * D));
+        po = ar.take((sp.f32 ? sizeof(float) : sizeof(_Float16)) * splits * it.T * Hq * D);
         pml = static_cast<float*>(ar.take(sizeof(float) * 2 * splits * it.T * Hq));
       }
       RopeSeq& r = L.rope.seq[L.rope.n_seq++];
@@ -753,6 +797,7 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       s.out = it.out;
       s.part_o = po;
       s.part_ml = pml;
+      s.part_f32 = sp.f32;
       s.L_keep = (int32_t)it.L_keep;
       s.T = (int32_t)it.T;
       s.n_tiles = tiles;
@@ -761,6 +806,7 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       s.head_tiles = head_tiles;
       item_total += Hkv * splits * tiles;
       if (splits > 1) {
+        L.merge.part_f32 |= sp.f32;
         L.merge.row_begin[L.merge.n_seq] = mrows;
         L.merge.seq[L.merge.n_seq++] = s;
         mrows += (int)(it.T * Hq);

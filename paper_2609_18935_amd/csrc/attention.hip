@@ -46,6 +46,7 @@ namespace tu {
 namespace {
 
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(8 * sizeof(float)))) float f32x8;
 
 constexpr int kBM = kAttnRows;
 constexpr int kBN = kAttnKeys;
@@ -379,8 +380,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const float l_tot = __builtin_bit_cast(float, (uint32_t)lsw[0]) + __builtin_bit_cast(float, (uint32_t)lsw[1]);
   if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  if (S.n_splits == 1) {
-    float* orow = S.out + ((long)t * Hq + qh) * D;
+  const long prow = (long)split * T * Hq + (long)t * Hq + qh;   // split is 0 in a whole run
+  if (S.n_splits == 1 || S.part_f32) {
+    float* orow = (S.n_splits == 1 ? S.out : (float*)S.part_o) + prow * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -389,8 +391,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         *(f32x4*)(orow + db * 32 + 8 * i + 4 * hl) = v;
       }
   } else {
-    const long prow = (long)split * T * Hq + (long)t * Hq + qh;
-    _Float16* orow = S.part_o + prow * D;
+    _Float16* orow = (_Float16*)S.part_o + prow * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -399,10 +400,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                    (_Float16)(o[db][4 * i + 2] * inv), (_Float16)(o[db][4 * i + 3] * inv)};
         *(f16x4*)(orow + db * 32 + 8 * i + 4 * hl) = v;
       }
-    if (hl == 0) {
-      S.part_ml[prow * 2] = l_tot > 0.f ? m_run : -__builtin_inff();
-      S.part_ml[prow * 2 + 1] = l_tot;
-    }
+  }
+  if (S.n_splits > 1 && hl == 0) {
+    S.part_ml[prow * 2] = l_tot > 0.f ? m_run : -__builtin_inff();
+    S.part_ml[prow * 2 + 1] = l_tot;
   }
 }
 
@@ -411,7 +412,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // splits l, l + split_lanes, ... in batches of 8 whose loads are all in flight
 // together (the running max and sums move between batches); the lanes' partial
 // results are then combined by shuffles and the first lane writes the row's 8 outputs.
-template <int D>
+// F32: contexts of the launch may have fp32 partials (33 registers more, so launches
+// without any take the instance that knows f16 only).
+template <int D, bool F32>
 __global__ __launch_bounds__(256) void k_attn_merge(MergeArgs a) {
   constexpr int TPR = D / 8;  // 8-dim pieces per row
   const int SL = a.split_lanes;
@@ -432,42 +435,47 @@ __global__ __launch_bounds__(256) void k_attn_merge(MergeArgs a) {
     const long row = g - a.row_begin[si];
     orow = S.out + row * D + 8 * d8;
     const long R = (long)S.T * a.n_q_heads;
-    for (int s0 = sl; s0 < S.n_splits; s0 += 8 * SL) {
-      f32x2 ml[8];
-      f16x8 v[8];
+    auto sum_splits = [&](auto zero) __attribute__((always_inline)) {
+      typedef decltype(zero) part8;   // 8 dims of a partial output
+      for (int s0 = sl; s0 < S.n_splits; s0 += 8 * SL) {
+        f32x2 ml[8];
+        part8 v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int sp = s0 + j * SL;
-        const long at = (long)sp * R + row;
-        if (sp < S.n_splits) {
-          ml[j] = *(const f32x2*)(S.part_ml + at * 2);
-          v[j] = *(const f16x8*)(S.part_o + at * D + 8 * d8);
-        } else {
-          ml[j] = f32x2{-__builtin_inff(), 0.f};
-          v[j] = f16x8{};
+        for (int j = 0; j < 8; ++j) {
+          const int sp = s0 + j * SL;
+          const long at = (long)sp * R + row;
+          if (sp < S.n_splits) {
+            ml[j] = *(const f32x2*)(S.part_ml + at * 2);
+            v[j] = ((const part8*)S.part_o)[at * TPR + d8];
+          } else {
+            ml[j] = f32x2{-__builtin_inff(), 0.f};
+            v[j] = zero;
+          }
         }
-      }
-      float Mb = M;
+        float Mb = M;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) Mb = fmaxf(Mb, ml[j][0]);
-      if (Mb == -__builtin_inff()) continue;
-      const float c = M == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
-      L *= c;
-      acc0 *= c;
-      acc1 *= c;
+        for (int j = 0; j < 8; ++j) Mb = fmaxf(Mb, ml[j][0]);
+        if (Mb == -__builtin_inff()) continue;
+        const float c = M == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
+        L *= c;
+        acc0 *= c;
+        acc1 *= c;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (ml[j][0] == -__builtin_inff()) continue;
-        const float w = __builtin_amdgcn_exp2f(ml[j][0] - Mb) * ml[j][1];
-        L += w;
+        for (int j = 0; j < 8; ++j) {
+          if (ml[j][0] == -__builtin_inff()) continue;
+          const float w = __builtin_amdgcn_exp2f(ml[j][0] - Mb) * ml[j][1];
+          L += w;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc0[e] += w * (float)v[j][e];
-          acc1[e] += w * (float)v[j][4 + e];
+          for (int e = 0; e < 4; ++e) {
+            acc0[e] += w * (float)v[j][e];
+            acc1[e] += w * (float)v[j][4 + e];
+          }
         }
+        M = Mb;
       }
-      M = Mb;
-    }
+    };
+    if (F32 && S.part_f32) sum_splits(f32x8{});
+    else sum_splits(f16x8{});
   }
   // combine the lanes of a row group (every lane of the wave takes part in the shuffles)
   for (int x = 1; x < SL; x <<= 1) {
@@ -494,6 +502,21 @@ __global__ __launch_bounds__(256) void k_attn_merge(MergeArgs a) {
   *(f32x4*)(orow + 4) = acc1 * inv;
 }
 
+template <bool F32>
+hipError_t merge_for(const MergeArgs& a, int total_rows, int head_dim, hipStream_t s) {
+  const long threads = (long)total_rows * (head_dim / 8) * a.split_lanes;
+  const int blocks = (int)((threads + 255) / 256);
+  if (head_dim == 256)
+    hipLaunchKernelGGL((k_attn_merge<256, F32>), dim3(blocks), dim3(256), 0, s, a);
+  else if (head_dim == 128)
+    hipLaunchKernelGGL((k_attn_merge<128, F32>), dim3(blocks), dim3(256), 0, s, a);
+  else if (head_dim == 64)
+    hipLaunchKernelGGL((k_attn_merge<64, F32>), dim3(blocks), dim3(256), 0, s, a);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 }  // namespace
 
 static_assert(sizeof(AttnArgs) + sizeof(AttnOrder) <= kMaxKernargBytes, "attention launch record");
@@ -517,17 +540,7 @@ hipError_t launch_attention(const AttnArgs& a, const AttnOrder& o, int head_dim,
 hipError_t launch_attention_merge(const MergeArgs& a, int total_rows, int head_dim, hipStream_t s) {
   if (total_rows <= 0) return hipSuccess;
   if (a.split_lanes < 1 || a.split_lanes > 16 || (a.split_lanes & (a.split_lanes - 1))) return hipErrorInvalidValue;
-  const long threads = (long)total_rows * (head_dim / 8) * a.split_lanes;
-  const int blocks = (int)((threads + 255) / 256);
-  if (head_dim == 256)
-    hipLaunchKernelGGL(k_attn_merge<256>, dim3(blocks), dim3(256), 0, s, a);
-  else if (head_dim == 128)
-    hipLaunchKernelGGL(k_attn_merge<128>, dim3(blocks), dim3(256), 0, s, a);
-  else if (head_dim == 64)
-    hipLaunchKernelGGL(k_attn_merge<64>, dim3(blocks), dim3(256), 0, s, a);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  return a.part_f32 ? merge_for<true>(a, total_rows, head_dim, s) : merge_for<false>(a, total_rows, head_dim, s);
 }
 
 }  // namespace tu

@@ -288,9 +288,11 @@ __global__ __launch_bounds__(kThreads, D == 256 ? 1 : 2) void k_attn_short(AttnA
     const long at = (long)tt * Hq + h0 + (row - tt * G);
     if (S.n_splits == 1) {
       *(f32x4*)(S.out + at * D + 4 * c) = sum;
+    } else if (S.part_f32) {
+      *(f32x4*)((float*)S.part_o + ((long)split * T * Hq + at) * D + 4 * c) = sum;
     } else {
       const f16x4 hv = {(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
-      *(f16x4*)(S.part_o + ((long)split * T * Hq + at) * D + 4 * c) = hv;
+      *(f16x4*)((_Float16*)S.part_o + ((long)split * T * Hq + at) * D + 4 * c) = hv;
     }
   }
   if (S.n_splits > 1 && wave == 0 && hl == 0 && row_ok) {

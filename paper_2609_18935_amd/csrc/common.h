@@ -223,7 +223,7 @@ struct AttnSeq {
   const _Float16* vt;    // [Hkv][head_tiles][D * kVtRow] packed f16 V^T tiles (long kernel)
   const bf16_t* v_cache; // [cap][Hkv][D] (short kernel)
   float* out;            // [T][Hq][D]
-  _Float16* part_o;      // [splits][T*Hq][D] normalised split outputs (unused when splits == 1)
+  void* part_o;          // [splits][T*Hq][D] normalised split outputs, f16 or fp32 (unused when splits == 1)
   float* part_ml;        // [splits][T*Hq][2] (reference max in log2 units, sum)
   int32_t L_keep;
   int32_t T;
@@ -232,7 +232,7 @@ struct AttnSeq {
   int32_t item_begin;    // first attention workgroup of this context
   int32_t head_tiles;    // tiles per KV head in vt
   int32_t check_range;   // short kernel: report values beyond f16 (no packing launch does)
-  int32_t pad;
+  int32_t part_f32;      // part_o is fp32
 };
 
 struct AttnArgs {
@@ -267,6 +267,7 @@ struct MergeArgs {
   AttnSeq seq[kMaxSeqPerLaunch];
   int32_t n_seq;
   int32_t n_q_heads;
+  int32_t part_f32;      // some context's partial outputs are fp32
   int32_t split_lanes;   // lanes per 8 output dims of a row (1, 2, 4, 8 or 16), each a share of the splits
   int32_t row_begin[kMaxSeqPerLaunch + 1];  // prefix of T*Hq over contexts
 };

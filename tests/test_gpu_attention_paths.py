@@ -1,10 +1,11 @@
 """GPU tests of the attention launch's dispatch branches against the float64 oracle (MI355X only)."""
+import numpy as np
 import pytest
 import torch
 
 import synth
 import paper_2609_18935_amd as tu
-from gpu_cases import DEV, AttnCase, assert_close
+from gpu_cases import DEV, AttnCase, assert_close, sample_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +45,53 @@ def test_longest_first_order(Hq, Hkv, D, L, T, splits):
     case = _run(synth.AttnShape(Hq, Hkv, D), L, T, splits)
     ref = case.oracle([], L)
     assert_close(case.out.cpu().numpy(), ref["out"], "longest-first attention")
+
+
+def _rel2(got, want):
+    return float(np.linalg.norm(got.cpu().numpy().astype(np.float64) - want) / np.linalg.norm(want))
+
+
+# Launches split only for their uneven query tiles write fp32 partials: no further from
+# float64 than the same launch whole (probabilities in f16 on both sides; f16 partials are 1.5
+# times as far).
+@pytest.mark.parametrize("Hq,Hkv,D,L,T", [(16, 2, 256, 0, 2721), (16, 4, 64, 0, 3000)])
+def test_uneven_tiles_in_splits_lose_no_precision(Hq, Hkv, D, L, T):
+    print(f"[case] split for uneven tiles Hq={Hq} Hkv={Hkv} D={D} L={L} T={T}", flush=True)
+    shape = synth.AttnShape(Hq, Hkv, D)
+    rows = sample_rows(T, 200, 5)
+    case = _run(shape, L, T, 0)
+    want = case.oracle([], L, rows=rows)["out"]
+    split, whole = (_rel2(c.out[rows], want) for c in (case, _run(shape, L, T, 1)))
+    print(f"[parity] error {split:.3e}, whole {whole:.3e}", flush=True)
+    assert split <= 1.05 * whole
+
+
+# Short tails over few rows in splits: the bf16 rounding of the rotated queries is the oracle's
+# too, P has 16 bits and the partials are fp32, so only 2^-16 and fp32 sums remain; alone and
+# beside contexts whose partials are f16.
+@pytest.mark.parametrize("others", [(), (9000, 20000)])
+@pytest.mark.parametrize("Hq,Hkv,D,L,T", [(16, 2, 256, 300, 1), (16, 4, 64, 600, 16)])
+def test_short_tails_that_would_run_whole_lose_no_precision(Hq, Hkv, D, L, T, others):
+    print(f"[case] short tail Hq={Hq} Hkv={Hkv} D={D} L={L} T={T} beside {others}", flush=True)
+    shape = synth.AttnShape(Hq, Hkv, D)
+    cases = [AttnCase(shape, 26, 0, 0, n, T, char=i) for i, n in enumerate((L,) + others)]
+    ctxs = []
+    for c in cases:
+        ctx = tu.Context(c.capacity, device=DEV)
+        ctx.pos[:c.L_old] = torch.arange(c.L_old, dtype=torch.int32, device=DEV)
+        ctx.set_metadata([(0, c.L_old)], c.L_old)
+        ctxs.append(ctx)
+    out = torch.full((len(cases) * T, Hq, D), float("nan"), device=DEV)
+    layer = tu.LayerIO(tu.TU_LAYER_ATTN, torch.cat([c.q for c in cases]), torch.cat([c.k for c in cases]),
+                       torch.cat([c.v for c in cases]), out, k_cache=[c.k_cache for c in cases],
+                       v_cache=[c.v_cache for c in cases])
+    tu.update_layer_stack(ctxs, [[] for _ in cases], [T] * len(cases), [layer],
+                          tu.attn_params(Hq, Hkv, D, shape.rdim, shape.rope_theta, shape.softmax_scale))
+    for i, c in enumerate(cases):
+        err = _rel2(out[i * T:(i + 1) * T], c.oracle([], c.L_old)["out"])
+        print(f"[parity] context {i}: {err:.3e}", flush=True)
+        # beside longer contexts the first of 616 rows (10 key tiles) was split in f16 all along
+        assert err <= (2e-5 if i == 0 and (L == 300 or not others) else 1e-3)
 
 
 # The short-tail kernel: one to eight row tiles of 32, contexts of none to a few rows per
