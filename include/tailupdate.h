@@ -264,7 +264,8 @@ int commit_tail(tu_seq* seq, int64_t T);
  *   S <- g_t * S (I - beta_t k_t k_t^T) + beta_t v_t k_t^T,   o_t = scale * S q_t,
  * evaluated in chunks of p->chunk tokens (chunk-parallel WY preparation, then a
  * sequential chain over chunks with the fp32 state held on chip); tails of a few tokens
- * (at most 32) are evaluated token by token in fp32.
+ * (at most 20) are evaluated token by token in fp32. A context's results do not depend on
+ * what else is in the call.
  *  state: device fp32 [n_v_heads][d_v][d_k], updated in place.
  *  q, k:  device bf16 [T][n_k_heads][d_k];  v: device bf16 [T][n_v_heads][d_v].
  *  beta, g: device fp32 [T][n_v_heads];  out: device fp32 [T][n_v_heads][d_v].

@@ -883,13 +883,6 @@ struct DeltaItem {
   int64_t T;
 };
 
-// Longest tail for which a delta launch of `heads` (items x value heads) goes token by
-// token. With heads for at most one workgroup per CU's SIMDs a token costs 0.24 us of
-// latency: 4.0 us for one token, 11.4 for 32 (32 heads of 128), 18.9 for 64, against 15.2 for
-// prep and chain whatever the length. Launches of many heads are bound by the issue of
-// the row products instead: 36 items, 16 tokens 73 us (chunked 89), 24 tokens 99 us (89).
-int64_t step_tokens(int64_t heads) { return heads <= kCus / 2 ? kStepTokens : kStepTokens / 2; }
-
 // 16-column blocks of S (items x value heads x d / 16) up to which a delta launch takes the
 // direct chain: one workgroup per CU. One layer of 32 heads of 128, chunk 64 (staged /
 // direct chain, between events): 512 tokens 22.9 / 15.1 us, 2,048 tokens 65 / 40 us, 8,191
@@ -915,28 +908,22 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
   out->clear();
   for (size_t g0 = 0; g0 < items.size(); g0 += kMaxSeqPerDelta) {
     const size_t g1 = std::min(items.size(), g0 + kMaxSeqPerDelta);
-    int n_active = 0;
-    for (size_t i = g0; i < g1; ++i) n_active += items[i].T > 0;
-    // the staged chain: slice d_v (16 rows of S per owner wave) into as few workgroups per
-    // head as give half the CUs one (the rest serve the attention layers running
-    // beside the delta layers)
-    int dvs = std::min(DK, 64);
-    while (dvs > 16 && (int64_t)n_active * Hv * (DK / dvs) < kCus / 2) dvs /= 2;
-    DeltaArgs a{};
-    a.n_k_heads = p->n_k_heads;
-    a.n_v_heads = Hv;
-    a.scale = p->scale;
-    a.direct = (int64_t)n_active * Hv * (DK / 16) <= kDirectBlocks && beside_rows <= kDirectRows;
-    a.n_slices = a.direct ? DK / 16 : DK / dvs;
-    a.status = status;
-    int64_t longest = 0;
-    for (size_t i = g0; i < g1; ++i) longest = std::max(longest, items[i].T);
-    a.step = longest <= step_tokens((int64_t)n_active * Hv);
+    // tails of up to kStepTokens tokens go token by token, whatever else is in the launch: a
+    // context's results do not depend on its neighbours
+    DeltaArgs step{}, a{};
+    step.step = 1;
+    for (DeltaArgs* x : {&step, &a}) {
+      x->n_k_heads = p->n_k_heads;
+      x->n_v_heads = Hv;
+      x->scale = p->scale;
+      x->status = status;
+    }
     int chunks = 0;
     for (size_t i = g0; i < g1; ++i) {
       const auto& it = items[i];
       if (it.T <= 0) continue;
-      DeltaSeq& s = a.seq[a.n_seq++];
+      DeltaArgs& x = it.T <= kStepTokens ? step : a;
+      DeltaSeq& s = x.seq[x.n_seq++];
       s.q = it.q;
       s.k = it.k;
       s.v = it.v;
@@ -945,15 +932,21 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
       s.state = it.state;
       s.out = it.out;
       s.T = (int32_t)it.T;
+      if (x.step) continue;
       s.n_chunks = (int32_t)((it.T + C - 1) / C);
       s.chunk_begin = chunks;
       chunks += s.n_chunks;
     }
+    if (step.n_seq > 0) out->push_back(step);
+    if (a.n_seq == 0) continue;
     a.total_chunks = chunks;
-    if (a.step) {
-      if (a.n_seq > 0) out->push_back(a);
-      continue;
-    }
+    // the staged chain: slice d_v (16 rows of S per owner wave) into as few workgroups per
+    // head as give half the CUs one (the rest serve the attention layers running
+    // beside the delta layers)
+    int dvs = std::min(DK, 64);
+    while (dvs > 16 && (int64_t)a.n_seq * Hv * (DK / dvs) < kCus / 2) dvs /= 2;
+    a.direct = (int64_t)a.n_seq * Hv * (DK / 16) <= kDirectBlocks && beside_rows <= kDirectRows;
+    a.n_slices = a.direct ? DK / 16 : DK / dvs;
     Arena ar(ws);
     a.ws_w = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * DK));
     a.ws_tv = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * std::max(C, 32)));
@@ -962,7 +955,7 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
     a.ws_q = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * p->n_k_heads * C * DK));
     a.ws_kt = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * p->n_k_heads * DK * std::max(C, 32)));
     max_used = std::max(max_used, ar.used);
-    if (a.n_seq > 0) out->push_back(a);
+    out->push_back(a);
   }
   *ws_bytes = max_used;
   return TU_OK;

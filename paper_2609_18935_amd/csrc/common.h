@@ -286,7 +286,15 @@ struct DeltaSeq {
   int32_t pad;
 };
 
-constexpr int kStepTokens = 32;   // longest tail of the token-by-token delta kernel
+// Longest tail of the token-by-token delta kernel. A launch of few heads costs 0.24 us of
+// latency a token (4.0 us for one, 11.4 for 32, against 15 for prep and chain whatever the
+// length), one of many heads the issue of the row products; the line has to hold for both,
+// since a context's results must not depend on the launch it is in. Updates of 12 attention
+// and 36 delta layers over 8,000 rows (steps / chunks): 16 tokens 151.6 / 176.8 us, 20 tokens
+// 169.6 / 182.0, 24 tokens 185.5 / 187.3, 32 tokens 227.3 / 198.7; over 64,000 rows 20 tokens
+// 499.7 / 496.0, 24 tokens 535 / 519; 32 contexts of one and three layers 20 tokens 359 / 386,
+// 24 tokens 388 / 382; 36 delta layers alone 20 tokens 86.2 / 91.2, 24 tokens 100.3 / 91.8.
+constexpr int kStepTokens = 20;
 constexpr int kStepRows = 16;     // state rows of one of its workgroups
 
 struct DeltaArgs {
@@ -297,7 +305,7 @@ struct DeltaArgs {
   int32_t total_chunks;
   float scale;
   int32_t n_slices;      // d_v slices per value head in the chain kernel
-  int32_t step;          // every tail is at most kStepTokens: the token-by-token kernel (no workspace)
+  int32_t step;          // a launch of the token-by-token kernel (tails of up to kStepTokens, no workspace)
   int32_t direct;        // the chain reads its operands straight from the workspace (few heads)
   CallStatus status;     // kFaultRange when an f16 operand overflows
   // matrices of a chunk, in operand fragments (16 rows x 32 positions) as the chain reads them
