@@ -660,14 +660,24 @@ void plan_dies(const AttnArgs& a, int G, AttnOrder* o) {
   o->blocks = most * kXcds;
 }
 
-// When a launch takes the short-tail kernel: its contexts have at most kShortMaxRows packed
-// query rows (T x query heads per KV head), in at most two row tiles, or the whole launch
-// is at most kShortWork units (32 rows x 32 keys), 8 per wave of the chip. The short kernel
-// takes about 1.7 us per unit and wave, the long one 3.8 us per 256 rows x 64 keys however
-// few of the rows are used, plus its prologue and the V^T tiles. Measured (16/2 heads of
-// 256, V^T copy current; short / long kernel, us a call): 1 token over 32,768 rows 27.2 /
-// 34.6, 8 tokens 33.4 / 36.8, 16 tokens 42.1 / 41.4, 32 tokens 58.2 / 49.7; over 12,000 rows 8
-// tokens 25.9 / 29.1, 32 tokens 33.1 / 40.5.
+// When a launch takes the short-tail kernel: one row tile of kShortRows packed query rows (T x
+// query heads per KV head) per context whatever the caches' length; two if the whole launch is
+// at most 4 kShortWork units (32 rows x 32 keys); up to kShortMaxRows rows if it is at most
+// kShortWork units, 8 per wave of the chip. A unit takes a wave about 2.2, 1.1 or 0.7 us at
+// head_dim 256, 128 or 64; the long kernel takes 3.8, 1.9 or 1.3 us per 256 rows x 64 keys
+// however few of the rows are used, plus its prologue and the V^T tiles, but reads the keys
+// once for all its rows: with more row tiles the short kernel's second and third reading of
+// the cache costs more than that. Measured (V^T copy current, short / long kernel, us a call,
+// heads in the order query / KV / dim):
+//   one row tile, 16/2/256: 1 token over 32,768 rows 27.2 / 34.6, 12 layers over 64,000 rows
+//     297 / 322; 32/8/128: the same 12 layers 603 / 640; 16/4/64: 153 / 222
+//   two row tiles, 16/2/256: 12 layers over 21,325 rows (32,000 units) 130 / 137, 32 contexts of
+//     30,000 rows (120,064) 412 / 404; 32/8/128: 8 contexts of 7,984 rows (32,000) 59.0 / 70.5,
+//     12 layers over 12,000 rows (72,192) 178 / 154 and over 64,000 rows (384,192) 846 / 651;
+//     16/4/64: 12 layers over 10,650 rows (32,000) 51.5 / 51.7, over 32,000 rows (96,096) 138 / 129
+//   more, 16/2/256: 128 rows over 31,984 rows (8,000) 39.0 / 40.8, 256 rows over 15,968 rows (8,000)
+//     38.1 / 45.7, over 32,000 rows (16,016) 53.3 / 51.8; 32/8/128: 128 rows over 7,968 rows (8,000)
+//     25.7 / 26.5, over 32,000 rows (32,032) 49.8 / 41.8
 constexpr int64_t kShortMaxRows = 256;
 constexpr int64_t kShortWork = 8192;
 
@@ -715,7 +725,8 @@ int plan_attention(const tu_attn_params* p, std::vector<AttnItem>& items, void* 
       short_work += Hkv * ((rows + kShortRows - 1) / kShortRows) *
                     ((items[i].L_keep + items[i].T + kShortKeys - 1) / kShortKeys);
     }
-    L.short_tail = rows_most <= 2 * kShortRows || (rows_most <= kShortMaxRows && short_work <= kShortWork);
+    L.short_tail = rows_most <= kShortRows || (rows_most <= 2 * kShortRows && short_work <= 4 * kShortWork) ||
+                   (rows_most <= kShortMaxRows && short_work <= kShortWork);
     L.rope.n_q_heads = Hq;
     L.rope.n_kv_heads = Hkv;
     L.rope.head_dim = D;

@@ -52,3 +52,26 @@ def _splits(hq, hkv, d, T, rows):
 def test_partial_outputs_keep_fp32_where_a_launch_would_run_whole(hq, hkv, d, T, rows, split, size):
     n, b = _splits(hq, hkv, d, T, rows)
     assert (n > 1, b) == (split, size), (n, b)
+
+
+# A short tail packs no V^T tiles. One row tile of 32 packed rows: always; two: up to 32,768 units
+# of 32 rows and 32 keys; up to eight: up to 8,192.
+@pytest.mark.parametrize("hq,hkv,d,T,keys,short", [
+    (16, 2, 256, 1, 1 << 20, True),
+    (16, 2, 256, 4, 1 << 20, True),
+    (32, 8, 128, 8, 1 << 20, True),
+    (32, 8, 128, 9, 65536, True),
+    (32, 8, 128, 9, 65537, False),
+    (32, 8, 128, 16, 65536, True),
+    (32, 8, 128, 16, 65537, False),
+    (16, 2, 256, 8, 262144, True),
+    (16, 2, 256, 8, 262145, False),
+    (32, 8, 128, 17, 10912, True),       # three row tiles: 341 units of keys
+    (32, 8, 128, 17, 10913, False),
+    (16, 4, 64, 64, 8192, True),         # eight
+    (16, 4, 64, 64, 8193, False),
+    (16, 4, 64, 65, 1000, False),
+])
+def test_short_tail_limits(hq, hkv, d, T, keys, short):
+    tiles = 0 if short else _up(2 * hkv * ((keys + 63) // 64) * d * 72)
+    assert _size(hq, hkv, d, T, keys - T, 1) == 256 + _up(2 * T * hq * d) + tiles
