@@ -881,8 +881,8 @@ def workload_stage_fracs(cfg, rounds, kern):
     work = {
         "attention": (["rope_vt_pack", "attention", "attention_merge"], "mfma",
                       attention_flops(cfg, rounds) * kinds.count("attn") / 1e12, "TFLOP/s", MFMA16_PEAK_TFLOPS),
-        "delta": (["delta_prep", "delta_chain"], "hbm", delta_bytes(cfg, rounds) * kinds.count("delta") / 1e9,
-                  "GB/s", HBM_PEAK_GBS),
+        "delta": (["delta_prep", "delta_chain", "delta_chain_direct"], "hbm",
+                  delta_bytes(cfg, rounds) * kinds.count("delta") / 1e9, "GB/s", HBM_PEAK_GBS),
         "compaction": (["compact"], "hbm", gather_bytes(cfg, rounds) * kinds.count("attn") / 1e9, "GB/s",
                        HBM_PEAK_GBS),
     }
@@ -891,7 +891,7 @@ def workload_stage_fracs(cfg, rounds, kern):
         ms = sum(kern[k]["ms_per_step"] for k in ks if k in kern)
         if ms > 0 and units > 0:
             ach = units / (ms / 1e3)
-            stages[name] = {"kernels": ks, "ms_per_step": round(ms, 5), "bound": bound, "achieved": round(ach, 3),
+            stages[name] = {"kernels": [k for k in ks if k in kern], "ms_per_step": round(ms, 5), "bound": bound, "achieved": round(ach, 3),
                             "peak": peak, "unit": unit, "frac": round(ach / peak, 4)}
     return stages
 

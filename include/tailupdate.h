@@ -487,7 +487,7 @@ int attention_tv_distance(const float* p, const float* q, const int32_t* q_row_o
  * (or a negative status) and clears the records. Names (one per launch or pair
  * of launches): compact (keep-scan, then gather), rope_vt_pack (RoPE + append of
  * the tail with the V^T packing of the key tiles), attention, attention_merge,
- * delta_prep, delta_chain, delta_step, short_conv, relocate, probe, group_mass, tv_distance.
+ * delta_prep, delta_chain or delta_chain_direct, delta_step, short_conv, relocate, probe, group_mass, tv_distance.
  */
 int tu_profile_enable(int on);
 int tu_profile_collect(char* names, int32_t name_stride, int32_t* counts, double* total_ms, int32_t max_entries);

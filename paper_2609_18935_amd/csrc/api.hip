@@ -902,14 +902,21 @@ struct DeltaItem {
 // eight layers take 205 / 466 us.
 constexpr int64_t kDirectBlocks = kCus;
 
-// Cache rows, over the layers and contexts of the attention that runs beside a delta launch,
-// up to which that launch takes the direct chain. It ends sooner than the staged chain but
-// holds twice the CUs, more CU time in all: an attention that fills the chip for longer than
-// the chain pays for it. Update of one attention and one delta layer (staged / direct): 1,072
-// tokens over 5,751 rows 178.3 / 174.0 us, 870 over 6,934 rows 172.6 / 166.2 us, 564 over
-// 11,472 rows 174.8 / 174.7 us, 637 over 37,031 rows 421.4 / 424.3 us, 303 over 40,235 rows
-// 243.0 / 244.1 us, 861 over 63,046 rows 897 / 903 us.
+// Beside attention a launch of more than half the CUs' blocks takes the direct chain only up
+// to this many cache rows (those the attention reads, over its layers and contexts) and this
+// tail. The direct chain ends sooner than the staged one but holds twice the CUs, more CU time
+// in all: an attention that fills the chip for longer than the chain pays for it; launches of
+// up to half the CUs' blocks hold no more CUs than the staged chain. Direct against staged time
+// of an update of one attention and one delta layer, T replaced tokens:
+//   256 blocks (32 heads of 128), 16/2 heads of 256: 6,000 rows T 512 -1.2 %, 1,024 -2.3 %, 1,792
+//     -5.5 %, 2,048 +3.5 %; 12,000 rows T 1,280 -2.9 %, 1,792 -2.2 %, 2,048 +2.4 %; 20,000 rows -1.3 to
+//     +1.2 %, 2,048 +1.5 %; 30,000 rows -0.3 to +1.2 %, 2,048 +2.2 %; 64,000 rows -0.2 to +1.0 %
+//   the same, 32/8 heads of 128: 6,000 rows T 1,100 -5.0 %, 1,792 -4.0 %, 2,048 +2.5 %; 12,000 rows
+//     -1.9 to -0.9 %, 2,048 +0.4 %; 20,000 rows -0.3 to +1.0 %; 30,000 rows 0 to +0.9 %
+//   128 blocks (16 heads of 128, chunk 32): 16/2 heads of 256, 6,000 rows T 2,048 -7.1 %, 25,000 rows
+//     -1.8 %, 64,000 rows +0.2 %; 16/4 heads of 64, 6,000 rows T 2,048 -15.8 %, 64,000 rows -3.5 %
 constexpr int64_t kDirectRows = 12288;
+constexpr int64_t kDirectTail = 1792;
 
 // `beside_rows`: cache rows of the attention layers that run beside these items
 int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, void* ws, const CallStatus& status,
@@ -930,9 +937,11 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
       x->status = status;
     }
     int chunks = 0;
+    int64_t longest = 0;
     for (size_t i = g0; i < g1; ++i) {
       const auto& it = items[i];
       if (it.T <= 0) continue;
+      longest = std::max(longest, it.T);
       DeltaArgs& x = it.T <= kStepTokens ? step : a;
       DeltaSeq& s = x.seq[x.n_seq++];
       s.q = it.q;
@@ -956,7 +965,8 @@ int plan_delta(const tu_delta_params* p, const std::vector<DeltaItem>& items, vo
     // beside the delta layers)
     int dvs = std::min(DK, 64);
     while (dvs > 16 && (int64_t)a.n_seq * Hv * (DK / dvs) < kCus / 2) dvs /= 2;
-    a.direct = (int64_t)a.n_seq * Hv * (DK / 16) <= kDirectBlocks && beside_rows <= kDirectRows;
+    const bool room = beside_rows == 0 || (beside_rows <= kDirectRows && longest <= kDirectTail);
+    a.direct = (int64_t)a.n_seq * Hv * (DK / 16) <= (room ? kDirectBlocks : kDirectBlocks / 2);
     a.n_slices = a.direct ? DK / 16 : DK / dvs;
     Arena ar(ws);
     a.ws_w = static_cast<_Float16*>(ar.take(sizeof(_Float16) * (size_t)chunks * Hv * C * DK));
@@ -979,7 +989,7 @@ int run_delta(const std::vector<DeltaArgs>& ls, const tu_delta_params* p, hipStr
       continue;
     }
     if (int e = hip_check(timed("delta_prep", st, [&] { return launch_delta_prep(a, p->d_k, p->chunk, st); }), "delta-prep launch")) return e;
-    if (int e = hip_check(timed("delta_chain", st, [&] { return launch_delta_chain(a, p->d_k, p->chunk, st); }), "delta-chain launch")) return e;
+    if (int e = hip_check(timed(a.direct ? "delta_chain_direct" : "delta_chain", st, [&] { return launch_delta_chain(a, p->d_k, p->chunk, st); }), "delta-chain launch")) return e;
   }
   return TU_OK;
 }
@@ -1993,7 +2003,7 @@ int update_layer_stack(const tu_update* u, void* workspace, size_t workspace_byt
       std::vector<DeltaArgs> ls;
       int64_t rows = 0;
       for (int s = 0; s < u->n_seq; ++s)
-        if (u->seqs[s].T > 0) rows += sp.n_attn * (u->seqs[s].seq->len + u->seqs[s].T);
+        if (u->seqs[s].T > 0) rows += sp.n_attn * (u->seqs[s].seq->len - sp.rc[s].removed + u->seqs[s].T);
       plan_delta(&u->delta, items, ws_delta, status, &ls, &b, rows);
       if (int e = run_delta(ls, &u->delta, sd)) return e;
       if (side)

@@ -1,9 +1,9 @@
 """GPU tests of both delta-rule chains against the float64 oracle (MI355X only).
 
 Launches of at most 256 blocks of 16 state columns (items x value heads x d / 16) take the
-direct chain, larger ones and those beside attention over more than 12,288 cache rows the
-staged one: every head size and chunk length on both sides of the limits, whole and ragged
-chunks, one chunk.
+direct chain, larger ones the staged one, and so do those of more than 128 blocks beside
+attention over many rows or with a long tail: every head size and chunk length on both sides
+of the limits, whole and ragged chunks, one chunk.
 """
 import pytest
 import torch
@@ -67,21 +67,39 @@ def test_direct_chain_over_many_chunks_and_contexts(chunk):
         at += T
 
 
-@pytest.mark.parametrize("layers", [1, 2])
-@pytest.mark.parametrize("over", [0, 1])
-def test_chains_beside_attention_match_oracle(layers, over):
-    """Attention layers over exactly 12,288 cache rows, and over one row more each."""
-    T, rows = 100, 12288 // layers + over
-    print(f"[case] delta chain beside {layers} attention layers of {rows} rows", flush=True)
-    a, s = synth.AttnShape(2, 1, 64), synth.DeltaShape(2, 4, 128, 128, 32)
-    acs = [AttnCase(a, 43, 0, i, rows - T, T) for i in range(layers)]
+# Beside attention: launches of more than 128 blocks (16 heads of 128) up to 12,288 cache rows
+# over the attention layers, without the rows the call removes, and 1,792 tokens; others always.
+@pytest.mark.parametrize("layers,rows,removed,T,hv,direct", [
+    (1, 12288, 0, 100, 32, True),
+    (1, 12289, 0, 100, 32, False),
+    (2, 6144, 0, 100, 32, True),
+    (2, 6145, 0, 100, 32, False),
+    (1, 12288, 50, 100, 32, True),
+    (1, 12289, 50, 100, 32, False),
+    (1, 4000, 0, 1792, 18, True),
+    (1, 4000, 0, 1793, 18, False),
+    (1, 12289, 0, 100, 16, True),
+    (1, 12289, 0, 100, 18, False),
+])
+def test_chains_beside_attention_match_oracle(layers, rows, removed, T, hv, direct):
+    print(f"[case] delta chain, {hv} heads, {T} tokens, beside {layers} attention layers of {rows} rows", flush=True)
+    a, s = synth.AttnShape(2, 1, 64), synth.DeltaShape(hv // 2, hv, 128, 128, 32)
+    old = rows - T + removed
+    acs = [AttnCase(a, 43, 0, i, old, T) for i in range(layers)]
     c = DeltaCase(s, 43, 0, layers, T)
-    ctx = tu.Context(rows, device=DEV)
-    ctx.pos[:rows - T] = torch.arange(rows - T, dtype=torch.int32, device=DEV)
-    ctx.set_metadata([(0, rows - T)], rows - T)
+    ctx = tu.Context(old + T, device=DEV)
+    ctx.pos[:old] = torch.arange(old, dtype=torch.int32, device=DEV)
+    ctx.set_metadata([(0, old)], old)
     io = [tu.LayerIO(tu.TU_LAYER_ATTN, x.q, x.k, x.v, x.out, k_cache=[x.k_cache], v_cache=[x.v_cache]) for x in acs]
     io.append(tu.LayerIO(tu.TU_LAYER_DELTA, c.q, c.k, c.v, c.out, state=[c.state], beta=c.beta_d, g=c.g_d))
-    tu.update_layer_stack([ctx], [[]], [T], io, tu.attn_params(2, 1, 64, a.rdim, a.rope_theta), _params(s))
-    o, S = c.oracle()
-    assert_close(c.out.cpu().numpy(), o, "out")
-    assert_close(c.state.cpu().numpy(), S, "state")
+    tu.profile_enable(True)
+    try:
+        tu.update_layer_stack([ctx], [[(500, 500 + removed)] if removed else []], [T], io,
+                              tu.attn_params(2, 1, 64, a.rdim, a.rope_theta), _params(s))
+        kernels = tu.profile_collect()
+    finally:
+        tu.profile_enable(False)
+    assert ("delta_chain_direct" in kernels, "delta_chain" in kernels) == (direct, not direct)
+    vh, o, S = delta_oracle_heads(c.S0, c.q_b, c.k_b, c.v_b, c.beta, c.g, s.scale, [0, hv // 4, hv // 2 - 1])
+    assert_close(c.out.cpu().numpy()[:, vh], o, "out")
+    assert_close(c.state.cpu().numpy()[vh], S, "state")
