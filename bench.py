@@ -875,13 +875,17 @@ def summarize_diagnostics(out_dir, cfg_index):
 
 # ----------------------------------------------------------------------------- one workload
 
+# one layer's launches: chunks (prep, then either chain), or steps for a tail of a few tokens
+DELTA_KERNELS = ["delta_prep", "delta_chain", "delta_chain_direct", "delta_step"]
+
+
 def workload_stage_fracs(cfg, rounds, kern):
     """Algorithmic work per step of each stage against the summed durations of its kernels."""
     kinds = cfg.layer_kinds()
     work = {
         "attention": (["rope_vt_pack", "attention", "attention_merge"], "mfma",
                       attention_flops(cfg, rounds) * kinds.count("attn") / 1e12, "TFLOP/s", MFMA16_PEAK_TFLOPS),
-        "delta": (["delta_prep", "delta_chain", "delta_chain_direct"], "hbm",
+        "delta": (DELTA_KERNELS, "hbm",
                   delta_bytes(cfg, rounds) * kinds.count("delta") / 1e9, "GB/s", HBM_PEAK_GBS),
         "compaction": (["compact"], "hbm", gather_bytes(cfg, rounds) * kinds.count("attn") / 1e9, "GB/s",
                        HBM_PEAK_GBS),

@@ -1,6 +1,6 @@
 """Host logic of the benchmark (CPU only): the rocprofv3 summaries it writes under
 profiles/ (kernel table, copy-calibrated HBM bytes per dispatch, the attention traffic
-record and its staleness check), and its refusal of more than one GPU.
+record and its staleness check), the stages of a step, and its refusal of more than one GPU.
 
 The summaries are built from small synthetic CSV files laid out as rocprofv3 writes
 them, in a temporary directory; bench.ROOT is pointed there, so no committed profile
@@ -15,6 +15,7 @@ import sys
 import pytest
 
 import bench
+import synth
 
 ATTN = "void tu::(anonymous namespace)::k_attn<256>(tu::AttnArgs, tu::AttnOrder)"
 PART = "void tu::(anonymous namespace)::k_probe_part<256>(tu::ProbeArgs)"
@@ -98,6 +99,19 @@ def test_diagnostics_profile_summary(fake_root):
     assert "64.0 MiB (65,536 live rows" in md
     assert '"probe_ms": 0.6' in md
     assert "--only-diagnostics" in md and "--summarize-diagnostics" in md
+
+
+@pytest.mark.parametrize("kernels", [("delta_step",), ("delta_prep", "delta_chain"),
+                                     ("delta_prep", "delta_chain_direct"),
+                                     ("delta_step", "delta_prep", "delta_chain")])
+def test_delta_stage_counts_every_form_of_the_delta_rule(kernels):
+    """Short tails, the direct and the staged chain, and a step of several rounds."""
+    cfg = synth.CONFIGS[1]
+    rounds = [{"T": [32], "L_keep": [100], "ranges": [[]], "intervals": [[(0, 100)]]}]
+    stage = bench.workload_stage_fracs(cfg, rounds, {k: {"ms_per_step": 0.25} for k in kernels})["delta"]
+    assert stage["kernels"] == sorted(kernels, key=bench.DELTA_KERNELS.index)
+    assert stage["ms_per_step"] == 0.25 * len(kernels)
+    assert stage["achieved"] == pytest.approx(bench.delta_bytes(cfg, rounds) / (0.25e-3 * len(kernels)) / 1e9, rel=1e-3)
 
 
 def test_more_than_one_gpu_is_refused():
