@@ -681,6 +681,10 @@ void plan_dies(const AttnArgs& a, int G, AttnOrder* o) {
 constexpr int64_t kShortMaxRows = 256;
 constexpr int64_t kShortWork = 8192;
 
+// Workgroups of the short-tail kernel that a CU holds (132, 66.5 or 33.8 KB of LDS, 430, 204 or
+// 129 registers a wave).
+int short_per_cu(int head_dim) { return head_dim == 256 ? 1 : head_dim == 128 ? 2 : 3; }
+
 // Key-range splits of one context in a short-tail launch, in which one workgroup per CU
 // reads an equal share of the launch's units (`work`); a workgroup's four waves take at
 // least one unit each. A context of up to two units per wave (four of shorter rows) is not
@@ -2022,14 +2026,20 @@ int update_layer_stack(const tu_update* u, void* workspace, size_t workspace_byt
     // attention launch of kGateWaves or more full waves leaves no CU idle for the delta
     // layers to use, so it waits for them (they run beside the compaction and the
     // stage) instead of sharing CUs with them, which would only lengthen it by as much.
-    // Shorter launches leave CUs idle at their ragged end and keep the overlap.
+    // Shorter launches leave CUs idle at their ragged end and keep the overlap. Workgroups of
+    // the short-tail kernel count by the share of a CU that they hold (one token of 32
+    // contexts of 4,000 rows, 32/32 heads of 128, beside a delta layer: 446 us waiting, 436 us
+    // overlapped; 4 tokens over 1,000 rows 184 and 171 us).
     hipEvent_t gate = side ? side->join : nullptr;
     for (auto& items : stack_attn_groups(u, sp)) {
       size_t b = 0;
       std::vector<AttnLaunch> ls;
       plan_attention(&u->attn, items, ws_attn, status, &ls, &b);
       int64_t wgs = 0;
-      for (const auto& L : ls) wgs += L.order.blocks > 0 ? L.order.blocks : L.attn.total_items;
+      for (const auto& L : ls) {
+        const int per_cu = L.short_tail ? short_per_cu(u->attn.head_dim) : 1;
+        wgs += (L.order.blocks > 0 ? L.order.blocks : L.attn.total_items) / per_cu;
+      }
       const bool wait = gate && wgs >= (int64_t)kGateWaves * kCus;
       if (int e = run_attention(ls, u->attn.head_dim, st, wait ? gate : nullptr)) return e;
       if (wait) gate = nullptr;

@@ -5,7 +5,7 @@ import torch
 
 import synth
 import paper_2609_18935_amd as tu
-from gpu_cases import DEV, AttnCase, assert_close, sample_rows
+from gpu_cases import DEV, AttnCase, DeltaCase, assert_close, sample_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -146,6 +146,38 @@ def test_short_tail_many_contexts_in_one_call(vt):
         assert ctxs[i].vt_rows == L + T
         assert_close(out[at:at + T].cpu().numpy(), c.oracle([], L)["out"], f"context {i} (L={L}, T={T})")
         at += T
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_many_short_tails_beside_a_delta_layer(D):
+    """1,024 workgroups, of which a CU holds two or three, overlapping the delta layer."""
+    shape, ds, n = synth.AttnShape(32, 32, D), synth.DeltaShape(2, 4, 64, 64, 16), 32
+    print(f"[case] short tails of {n} contexts beside a delta layer, D={D}", flush=True)
+    cases = [AttnCase(shape, 27, 0, 0, 40 + 3 * i, 1, char=i) for i in range(n)]
+    deltas = [DeltaCase(ds, 27, 0, 1, 1, char=i) for i in range(n)]
+    ctxs = []
+    for c in cases:
+        ctx = tu.Context(c.capacity, device=DEV)
+        ctx.pos[:c.L_old] = torch.arange(c.L_old, dtype=torch.int32, device=DEV)
+        ctx.set_metadata([(0, c.L_old)], c.L_old)
+        ctxs.append(ctx)
+    out, dout = torch.full((n, 32, D), float("nan"), device=DEV), torch.full((n, 4, 64), float("nan"), device=DEV)
+    acat = lambda name: torch.cat([getattr(c, name) for c in cases])    # noqa: E731
+    dcat = lambda name: torch.cat([getattr(c, name) for c in deltas])   # noqa: E731
+    layers = [tu.LayerIO(tu.TU_LAYER_DELTA, dcat("q"), dcat("k"), dcat("v"), dout, state=[c.state for c in deltas],
+                         beta=dcat("beta_d"), g=dcat("g_d")),
+              tu.LayerIO(tu.TU_LAYER_ATTN, acat("q"), acat("k"), acat("v"), out, k_cache=[c.k_cache for c in cases],
+                         v_cache=[c.v_cache for c in cases])]
+    up = tu.update_layer_stack(ctxs, [[] for _ in cases], [1] * n, layers,
+                               tu.attn_params(32, 32, D, shape.rdim, shape.rope_theta, shape.softmax_scale),
+                               tu.delta_params(2, 4, 64, 64, 16, ds.scale))
+    torch.cuda.synchronize()
+    assert tu.workspace_faults(up.workspace) == 0
+    for i in (0, 7, 31):
+        assert_close(out[i:i + 1].cpu().numpy(), cases[i].oracle([], cases[i].L_old)["out"], f"context {i} attention")
+        o, S = deltas[i].oracle()
+        assert_close(dout[i:i + 1].cpu().numpy(), o, f"context {i} delta")
+        assert_close(deltas[i].state.cpu().numpy(), S, f"context {i} state")
 
 
 def test_short_tail_flags_values_beyond_f16():
