@@ -163,13 +163,17 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# The current stream's handle without the stream object that torch.cuda.current_stream() makes
+# (0.2 against 2.8 us), in torch versions that have it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        # NULL is the default stream; torch's current stream when a GPU is present, by its
-        # handle (0.2 us; the stream object torch.cuda.current_stream() makes takes 2.8)
+        # NULL is the default stream; torch's current stream when a GPU is present
         if not torch.cuda.is_available():
             return None
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return _raw_stream(torch._C._cuda_getDevice()) if _raw_stream else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

@@ -410,3 +410,15 @@ def test_vt_cache_bytes(L):
     assert L.tu_vt_cache_bytes(0, 2, 256) == 0
     assert L.tu_vt_cache_bytes(100, 2, 96) == 0
     assert L.tu_vt_cache_bytes(-1, 2, 256) == 0
+
+
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_stream_with_and_without_the_raw_handle(monkeypatch, raw):
+    """torch's call for the raw stream handle is private: where it is missing, the stream
+    object gives the handle."""
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 11}))
+    monkeypatch.setattr(B, "_raw_stream", (lambda device: 100 + device) if raw else None)
+    assert B._stream(None) == (103 if raw else 11)
+    assert B._stream(7) == 7 and B._stream(type("S", (), {"cuda_stream": 9})) == 9
