@@ -47,6 +47,29 @@ def test_longest_first_order(Hq, Hkv, D, L, T, splits):
     assert_close(case.out.cpu().numpy(), ref["out"], "longest-first attention")
 
 
+# The long kernel at its smallest: query tiles with few rows or with rows in some waves only,
+# whole and in splits (chosen and forced), past the short kernel's limits of rows (256) and
+# of units.
+@pytest.mark.parametrize("Hq,Hkv,D,L,T,splits", [
+    (16, 2, 256, 300, 33, 0),       # 264 rows: a second tile of 8
+    (16, 2, 256, 300, 33, 1),
+    (16, 2, 256, 300, 33, 5),
+    (16, 2, 256, 0, 36, 0),
+    (32, 4, 128, 777, 61, 3),       # 488 rows
+    (32, 8, 128, 11000, 17, 0),     # 68 rows over 345 units a row tile
+    (16, 4, 64, 8200, 64, 0),       # 256 rows
+    (16, 4, 64, 8200, 63, 64),
+    (16, 8, 64, 65530, 17, 0),      # 34 rows
+])
+def test_long_kernel_with_few_rows(Hq, Hkv, D, L, T, splits):
+    print(f"[case] long kernel Hq={Hq} Hkv={Hkv} D={D} L={L} T={T} splits={splits}", flush=True)
+    p = tu.attn_params(Hq, Hkv, D, kv_splits=1)
+    tiles = tu.lib().tail_prefill_attention_workspace_size(p, T, L) - 2 * T * Hq * D
+    assert tiles > 2 * Hkv * (L + T) * D, "no V^T tiles: the short kernel"
+    case = _run(synth.AttnShape(Hq, Hkv, D), L, T, splits)
+    assert_close(case.out.cpu().numpy(), case.oracle([], L)["out"], "long kernel")
+
+
 def _rel2(got, want):
     return float(np.linalg.norm(got.cpu().numpy().astype(np.float64) - want) / np.linalg.norm(want))
 
@@ -144,6 +167,12 @@ def test_short_tail_many_contexts_in_one_call(vt):
     at = 0
     for i, (c, (L, T)) in enumerate(zip(cases, sizes)):
         assert ctxs[i].vt_rows == L + T
+        if vt:   # the copy, refreshed with rows the launch does not read from it, is a fresh one's
+            fresh = tu.new_vt_cache(c.capacity, shape.n_kv_heads, shape.head_dim, DEV)
+            again = tu.Context(c.capacity, device=DEV)
+            again.set_metadata([(0, L + T)], L + T)
+            tu.refresh_vt_cache(again, [c.v_cache], [fresh])
+            assert torch.equal(vts[i].view(torch.int16), fresh.view(torch.int16)), f"context {i}: V^T copy"
         assert_close(out[at:at + T].cpu().numpy(), c.oracle([], L)["out"], f"context {i} (L={L}, T={T})")
         at += T
 

@@ -55,6 +55,9 @@ ROUNDS = [
     (np.array([[2900, 2950]]), 70, np.array([[0, 5]])),
     (np.zeros((0, 2), np.int64), 64, None),
     (np.array([[5, 40], [3100, 3120]]), 1, None),
+    # the copy that the single token left (its own attention reads V from the cache), read by
+    # the long kernel: more than 256 packed rows, and nothing moved that would repack it
+    (np.zeros((0, 2), np.int64), 40, None),
 ]
 
 
