@@ -41,6 +41,8 @@
 // by a table: longest first, each on the die with the least work so far.
 #include "attention_tile.h"
 
+#include <type_traits>
+
 namespace tu {
 
 namespace {
@@ -114,9 +116,10 @@ __device__ __forceinline__ int attn_item(const AttnArgs& a, const AttnOrder& o) 
   return (int)o.grp_item0[g] + slot - (g > g0 ? (int)o.grp_end[g - 1] : 0);
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn(AttnArgs a,
-                                                                                               AttnOrder ord) {
+// One workgroup's item. F32: a launch in splits whose partial outputs are fp32 (an instance of
+// its own: a third way out in one kernel made the whole runs of a 48-layer revision 0.7 % slower).
+template <int D, bool F32>
+__device__ __forceinline__ void attend(const AttnArgs& a, const AttnOrder& ord) {
   constexpr int NS = D / 16;                // 16-dim steps of S^T = K Q^T
   constexpr int NDB = D / 32;               // 32-dim blocks of O^T
   constexpr int RC = D / 8;                 // 16-byte chunks of data per K row
@@ -380,9 +383,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const float l_tot = __builtin_bit_cast(float, (uint32_t)lsw[0]) + __builtin_bit_cast(float, (uint32_t)lsw[1]);
   if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const long prow = (long)split * T * Hq + (long)t * Hq + qh;   // split is 0 in a whole run
-  if (S.n_splits == 1 || S.part_f32) {
-    float* orow = (S.n_splits == 1 ? S.out : (float*)S.part_o) + prow * D;
+  if (!F32 && S.n_splits == 1) {
+    float* orow = S.out + ((long)t * Hq + qh) * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -391,20 +393,35 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         *(f32x4*)(orow + db * 32 + 8 * i + 4 * hl) = v;
       }
   } else {
-    _Float16* orow = (_Float16*)S.part_o + prow * D;
+    const long prow = (long)split * T * Hq + (long)t * Hq + qh;
+    typedef std::conditional_t<F32, f32x4, f16x4> part4;
+    typedef std::conditional_t<F32, float, _Float16> part;
+    part* orow = (part*)S.part_o + prow * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        f16x4 v = {(_Float16)(o[db][4 * i] * inv), (_Float16)(o[db][4 * i + 1] * inv),
-                   (_Float16)(o[db][4 * i + 2] * inv), (_Float16)(o[db][4 * i + 3] * inv)};
-        *(f16x4*)(orow + db * 32 + 8 * i + 4 * hl) = v;
+        part4 v = {(part)(o[db][4 * i] * inv), (part)(o[db][4 * i + 1] * inv), (part)(o[db][4 * i + 2] * inv),
+                   (part)(o[db][4 * i + 3] * inv)};
+        *(part4*)(orow + db * 32 + 8 * i + 4 * hl) = v;
       }
+    if (hl == 0) {
+      S.part_ml[prow * 2] = l_tot > 0.f ? m_run : -__builtin_inff();
+      S.part_ml[prow * 2 + 1] = l_tot;
+    }
   }
-  if (S.n_splits > 1 && hl == 0) {
-    S.part_ml[prow * 2] = l_tot > 0.f ? m_run : -__builtin_inff();
-    S.part_ml[prow * 2 + 1] = l_tot;
-  }
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn(AttnArgs a,
+                                                                                               AttnOrder ord) {
+  attend<D, false>(a, ord);
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_f32(AttnArgs a,
+                                                                                                   AttnOrder ord) {
+  attend<D, true>(a, ord);
 }
 
 // Log-sum-exp merge of the split partials: `split_lanes` (1, 2, 4, 8 or 16) consecutive
@@ -526,15 +543,18 @@ hipError_t launch_attention(const AttnArgs& a, const AttnOrder& o, int head_dim,
   if (a.total_items <= 0) return hipSuccess;
   // without a die table the grid is rounded up to a multiple of 8 so the remap is a bijection
   const int blocks = o.n_groups > 0 ? o.blocks : (a.total_items + kXcds - 1) / kXcds * kXcds;
-  if (head_dim == 256)
-    hipLaunchKernelGGL(k_attn<256>, dim3(blocks), dim3(kThreads), 0, s, a, o);
-  else if (head_dim == 128)
-    hipLaunchKernelGGL(k_attn<128>, dim3(blocks), dim3(kThreads), 0, s, a, o);
-  else if (head_dim == 64)
-    hipLaunchKernelGGL(k_attn<64>, dim3(blocks), dim3(kThreads), 0, s, a, o);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  const bool f32 = a.seq[0].n_splits > 1 && a.seq[0].part_f32;   // the same for all its contexts
+  const auto run = [&](auto whole_or_f16, auto parts_f32) {
+    if (f32) hipLaunchKernelGGL(parts_f32, dim3(blocks), dim3(kThreads), 0, s, a, o);
+    else hipLaunchKernelGGL(whole_or_f16, dim3(blocks), dim3(kThreads), 0, s, a, o);
+    return hipGetLastError();
+  };
+  switch (head_dim) {
+    case 256: return run(k_attn<256>, k_attn_f32<256>);
+    case 128: return run(k_attn<128>, k_attn_f32<128>);
+    case 64: return run(k_attn<64>, k_attn_f32<64>);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_attention_merge(const MergeArgs& a, int total_rows, int head_dim, hipStream_t s) {

@@ -55,8 +55,10 @@ struct IntC {
   static constexpr int value = B;
 };
 
-template <int D>
-__global__ __launch_bounds__(kThreads, D == 256 ? 1 : 2) void k_attn_short(AttnArgs a, CallStatus status) {
+// One workgroup's item. F32: contexts of the launch may have fp32 partial outputs (an instance of
+// its own: the choice lengthens attn-turn's kernel, below, by 0.4 us).
+template <int D, bool F32>
+__device__ __forceinline__ void attend_short(const AttnArgs& a, const CallStatus& status) {
   constexpr int NS = D / 16;                 // 16-dim steps of S^T = K Q^T
   constexpr int NDB = D / 32;                // 32-dim blocks of O^T
   constexpr int RC = D / 8;                  // 16-byte chunks per V row
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(kThreads, D == 256 ? 1 : 2) void k_attn_short(AttnA
     const long at = (long)tt * Hq + h0 + (row - tt * G);
     if (S.n_splits == 1) {
       *(f32x4*)(S.out + at * D + 4 * c) = sum;
-    } else if (S.part_f32) {
+    } else if (F32 && S.part_f32) {
       *(f32x4*)((float*)S.part_o + ((long)split * T * Hq + at) * D + 4 * c) = sum;
     } else {
       const f16x4 hv = {(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
@@ -302,6 +304,16 @@ __global__ __launch_bounds__(kThreads, D == 256 ? 1 : 2) void k_attn_short(AttnA
   }
 }
 
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 256 ? 1 : 2) void k_attn_short(AttnArgs a, CallStatus status) {
+  attend_short<D, false>(a, status);
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 256 ? 1 : 2) void k_attn_short_f32(AttnArgs a, CallStatus status) {
+  attend_short<D, true>(a, status);
+}
+
 }  // namespace
 
 static_assert(sizeof(AttnArgs) + sizeof(CallStatus) <= kMaxKernargBytes, "short attention launch record");
@@ -309,15 +321,19 @@ static_assert(sizeof(AttnArgs) + sizeof(CallStatus) <= kMaxKernargBytes, "short 
 hipError_t launch_attention_short(const AttnArgs& a, const CallStatus& status, int head_dim, hipStream_t s) {
   if (a.total_items <= 0) return hipSuccess;
   const int blocks = (a.total_items + kXcds - 1) / kXcds * kXcds;   // a whole number per die (xcd_remap)
-  if (head_dim == 256)
-    hipLaunchKernelGGL(k_attn_short<256>, dim3(blocks), dim3(kThreads), 0, s, a, status);
-  else if (head_dim == 128)
-    hipLaunchKernelGGL(k_attn_short<128>, dim3(blocks), dim3(kThreads), 0, s, a, status);
-  else if (head_dim == 64)
-    hipLaunchKernelGGL(k_attn_short<64>, dim3(blocks), dim3(kThreads), 0, s, a, status);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  bool f32 = false;
+  for (int i = 0; i < a.n_seq; ++i) f32 = f32 || (a.seq[i].n_splits > 1 && a.seq[i].part_f32);
+  const auto run = [&](auto f16_only, auto any) {
+    if (f32) hipLaunchKernelGGL(any, dim3(blocks), dim3(kThreads), 0, s, a, status);
+    else hipLaunchKernelGGL(f16_only, dim3(blocks), dim3(kThreads), 0, s, a, status);
+    return hipGetLastError();
+  };
+  switch (head_dim) {
+    case 256: return run(k_attn_short<256>, k_attn_short_f32<256>);
+    case 128: return run(k_attn_short<128>, k_attn_short_f32<128>);
+    case 64: return run(k_attn_short<64>, k_attn_short_f32<64>);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace tu
