@@ -33,12 +33,14 @@
 // exchanges use v_permlane32_swap instead of an LDS round trip.
 //
 // For occupancy the key range is split over `n_splits` workgroups; each writes a
-// normalised f16 partial (O / l) with its reference max and sum, and k_attn_merge
-// combines them. Workgroups are ordered (context, kv head, split, tile); the query
-// tiles of one (context, head, split) key range go to one die (XCD) and share its L2.
-// A launch of one context gives every die an equal share of the items in this order;
-// a launch of several contexts, whose key ranges differ in length, places the groups
-// by a table: longest first, each on the die with the least work so far.
+// normalised partial (O / l; f16, or fp32 where the launch would run whole if its query
+// tiles were equal) with its reference max and sum, and k_attn_merge combines them.
+// Items are numbered (context, kv head, split, tile). A launch of one context gives every
+// die (XCD) an equal share of them in this order, so that the query tiles of one key range
+// share a die's L2; where its query tiles differ in length and fill the chip more than once
+// they run longest first, spread over the dies, instead. A launch of several contexts, whose
+// key ranges differ in length, places the groups of one key range by a table: longest first,
+// each on the die with the least work so far.
 #include "attention_tile.h"
 
 #include <type_traits>
