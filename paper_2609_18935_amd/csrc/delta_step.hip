@@ -84,10 +84,13 @@ __global__ __launch_bounds__(kThreads) void k_delta_step(DeltaArgs a) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) st[c + e] = x[e];
   }
-  uint32_t big16 = 0;   // largest |bf16| bits of q, k, v staged by this thread (two per word)
+  // largest |bf16| of q, k, v staged by this thread (two per word); fmaxf passes over NaN, which
+  // is no overflow, as the chunked form does
+  float big = 0.f;
   auto seen = [&](u32x4 w) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) big16 = max(big16, max(w[e] & 0x7FFFu, (w[e] >> 16) & 0x7FFFu));
+    for (int e = 0; e < 4; ++e)
+      big = fmaxf(big, fmaxf(fabsf(__uint_as_float(w[e] << 16)), fabsf(__uint_as_float(w[e] & 0xFFFF0000u))));
   };
   for (int e = tid; e < T * V8; e += kThreads) {
     const int t = e / V8, c = (e - t * V8) * 8;
@@ -110,7 +113,6 @@ __global__ __launch_bounds__(kThreads) void k_delta_step(DeltaArgs a) {
   }
   __syncthreads();
 
-  float big = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) big = fmaxf(big, fabsf(st[c]));
   float* out = S.out + (long)h * DK + i0 + row;
@@ -158,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void k_delta_step(DeltaArgs a) {
   for (int c = 0; c < NC; ++c) big = fmaxf(big, fabsf(st[c]));
 #pragma unroll
   for (int c = 0; c < NC; c += 4) *(f32x4*)(sp + c) = f32x4{st[c], st[c + 1], st[c + 2], st[c + 3]};
-  if (big > kF16Max || big16 >= 0x4780u) status_raise(a.status, kFaultRange);   // 0x4780: bf16 bits of 2^16
+  if (big > kF16Max) status_raise(a.status, kFaultRange);
 }
 
 }  // namespace

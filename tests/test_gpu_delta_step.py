@@ -57,6 +57,21 @@ def test_step_flags_values_beyond_f16_and_reports_its_call():
         assert bool(tu.workspace_faults(ws) & tu.TU_FAULT_RANGE) == big
 
 
+@pytest.mark.parametrize("T", [3, 20, 21])
+@pytest.mark.parametrize("name", ["q", "k", "v", "state"])
+def test_nan_is_no_overflow_in_either_form(name, T):
+    """A NaN reaches the outputs without a range report, token by token as in chunks; an
+    infinity is reported."""
+    s = synth.DeltaShape(2, 4, 128, 128, 64)
+    for bad, faults in ((float("nan"), 0), (float("inf"), tu.TU_FAULT_RANGE)):
+        print(f"[case] delta rule, {bad} in {name}, T={T}", flush=True)
+        c = DeltaCase(s, 35, 0, 0, T)
+        getattr(c, name)[(2 if name != "state" else 0, 1, 7)] = bad
+        ws = tu.delta_rule_continue(c.state, c.q, c.k, c.v, c.beta_d, c.g_d, _params(s), c.out)
+        assert tu.workspace_faults(ws) == faults
+        assert not bool(torch.isfinite(c.out).all())
+
+
 def test_step_in_a_stack_of_mixed_tails():
     """A call with tails of 0, 1 and 20 tokens, and one whose longest tail is chunked."""
     s = synth.DeltaShape(2, 4, 128, 128, 64)
