@@ -688,7 +688,12 @@ int short_per_cu(int head_dim) { return head_dim == 256 ? 1 : head_dim == 128 ? 
 // Key-range splits of one context in a short-tail launch, in which one workgroup per CU
 // reads an equal share of the launch's units (`work`); a workgroup's four waves take at
 // least one unit each. A context of up to two units per wave (four of shorter rows) is not
-// split: the merge launch would take longer.
+// split: the merge launch would take longer. One workgroup per CU also where a CU holds two
+// or three: shares for all that fit leave more partials to merge and fewer units to hide a wave's
+// prologue behind. One per CU / all that fit, us a call: 32/8 heads of 128, 1 token over 12,000
+// rows 23.4 / 24.6, 32,768 rows 34.2 / 34.6, 64,000 rows 51.9 / 51.6; 16/2 heads of 128 over 32,768
+// rows, 1 token 21.2 / 20.7, 8 tokens 23.6 / 25.2; 16/4 heads of 64, 1 token over 32,768 rows 20.1 /
+// 20.5; shorter caches the same.
 Splits short_splits(const tu_attn_params* p, int64_t L_keep, int64_t T, int64_t work, int64_t base_items,
                     bool uniform) {
   if (p->kv_splits > 0) return {p->kv_splits, false};
