@@ -527,8 +527,8 @@ double split_time(const tu_attn_params* p, const TileSpan& span, int64_t T, int6
   const int64_t waves = (base_items * s + kCus - 1) / kCus;
   const int64_t longest = (span.hi + s - 1) / s, shortest = (span.lo + s - 1) / s;
   // lengths fall evenly from longest to shortest; paired waves fill each other's gaps
-  double tiles = (double)longest;
-  if (waves > 1) {
+  double tiles = (double)(longest == shortest ? waves * longest : longest);
+  if (waves > 1 && longest > shortest) {
     const auto at = [&](int64_t wave) {
       return (double)longest - (double)(longest - shortest) * (double)(wave * kCus) / (double)(base_items * s);
     };
