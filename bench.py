@@ -761,7 +761,8 @@ def _profile_tables(out_dir):
 
     def short(n):
         n = n.replace("tu::(anonymous namespace)::", "").replace("void ", "")
-        return re.sub(r"\(.*\)$", "", n)
+        n = re.sub(r"\(.*\)$", "", n)
+        return re.sub(r", false>$", ">", n)   # attention without fp32 partial outputs: the plain name
 
     def rows(sub, name):
         path = os.path.join(out_dir, sub, name)

@@ -118,10 +118,13 @@ __device__ __forceinline__ int attn_item(const AttnArgs& a, const AttnOrder& o) 
   return (int)o.grp_item0[g] + slot - (g > g0 ? (int)o.grp_end[g - 1] : 0);
 }
 
-// One workgroup's item. F32: a launch in splits whose partial outputs are fp32 (an instance of
-// its own: a third way out in one kernel made the whole runs of a 48-layer revision 0.7 % slower).
+// F32: a launch in splits whose partial outputs are fp32 (an instance of its own: a third way
+// out in one kernel made a 48-layer revision 0.7 % slower; the body in an inlined function under two
+// kernels changed the prologue of both, 1,722 tokens over 14,447 rows of 16/4 heads of 64 167.1 ->
+// 168.9 us).
 template <int D, bool F32>
-__device__ __forceinline__ void attend(const AttnArgs& a, const AttnOrder& ord) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn(AttnArgs a,
+                                                                                               AttnOrder ord) {
   constexpr int NS = D / 16;                // 16-dim steps of S^T = K Q^T
   constexpr int NDB = D / 32;               // 32-dim blocks of O^T
   constexpr int RC = D / 8;                 // 16-byte chunks of data per K row
@@ -414,16 +417,47 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const AttnOrder& ord) 
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn(AttnArgs a,
-                                                                                               AttnOrder ord) {
-  attend<D, false>(a, ord);
-}
-
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_f32(AttnArgs a,
-                                                                                                   AttnOrder ord) {
-  attend<D, true>(a, ord);
+// Adds one lane's splits of a row piece (8 dims, part8 as the partials are held) to its running
+// max, sum and output.
+template <typename part8, int TPR>
+__device__ __forceinline__ void sum_splits(const AttnSeq& S, long R, long row, int d8, int sl, int SL, float& M, float& L,
+                                           f32x4& acc0, f32x4& acc1) {
+  for (int s0 = sl; s0 < S.n_splits; s0 += 8 * SL) {
+    f32x2 ml[8];
+    part8 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int sp = s0 + j * SL;
+      const long at = (long)sp * R + row;
+      if (sp < S.n_splits) {
+        ml[j] = *(const f32x2*)(S.part_ml + at * 2);
+        v[j] = ((const part8*)S.part_o)[at * TPR + d8];
+      } else {
+        ml[j] = f32x2{-__builtin_inff(), 0.f};
+        v[j] = part8{};
+      }
+    }
+    float Mb = M;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) Mb = fmaxf(Mb, ml[j][0]);
+    if (Mb == -__builtin_inff()) continue;
+    const float c = M == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
+    L *= c;
+    acc0 *= c;
+    acc1 *= c;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (ml[j][0] == -__builtin_inff()) continue;
+      const float w = __builtin_amdgcn_exp2f(ml[j][0] - Mb) * ml[j][1];
+      L += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc0[e] += w * (float)v[j][e];
+        acc1[e] += w * (float)v[j][4 + e];
+      }
+    }
+    M = Mb;
+  }
 }
 
 // Log-sum-exp merge of the split partials: `split_lanes` (1, 2, 4, 8 or 16) consecutive
@@ -454,47 +488,12 @@ __global__ __launch_bounds__(256) void k_attn_merge(MergeArgs a) {
     const long row = g - a.row_begin[si];
     orow = S.out + row * D + 8 * d8;
     const long R = (long)S.T * a.n_q_heads;
-    auto sum_splits = [&](auto zero) __attribute__((always_inline)) {
-      typedef decltype(zero) part8;   // 8 dims of a partial output
-      for (int s0 = sl; s0 < S.n_splits; s0 += 8 * SL) {
-        f32x2 ml[8];
-        part8 v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int sp = s0 + j * SL;
-          const long at = (long)sp * R + row;
-          if (sp < S.n_splits) {
-            ml[j] = *(const f32x2*)(S.part_ml + at * 2);
-            v[j] = ((const part8*)S.part_o)[at * TPR + d8];
-          } else {
-            ml[j] = f32x2{-__builtin_inff(), 0.f};
-            v[j] = zero;
-          }
-        }
-        float Mb = M;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) Mb = fmaxf(Mb, ml[j][0]);
-        if (Mb == -__builtin_inff()) continue;
-        const float c = M == -__builtin_inff() ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
-        L *= c;
-        acc0 *= c;
-        acc1 *= c;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          if (ml[j][0] == -__builtin_inff()) continue;
-          const float w = __builtin_amdgcn_exp2f(ml[j][0] - Mb) * ml[j][1];
-          L += w;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc0[e] += w * (float)v[j][e];
-            acc1[e] += w * (float)v[j][4 + e];
-          }
-        }
-        M = Mb;
-      }
-    };
-    if (F32 && S.part_f32) sum_splits(f32x8{});
-    else sum_splits(f16x8{});
+    if constexpr (F32) {
+      if (S.part_f32) sum_splits<f32x8, TPR>(S, R, row, d8, sl, SL, M, L, acc0, acc1);
+      else sum_splits<f16x8, TPR>(S, R, row, d8, sl, SL, M, L, acc0, acc1);
+    } else {
+      sum_splits<f16x8, TPR>(S, R, row, d8, sl, SL, M, L, acc0, acc1);
+    }
   }
   // combine the lanes of a row group (every lane of the wave takes part in the shuffles)
   for (int x = 1; x < SL; x <<= 1) {
@@ -552,9 +551,9 @@ hipError_t launch_attention(const AttnArgs& a, const AttnOrder& o, int head_dim,
     return hipGetLastError();
   };
   switch (head_dim) {
-    case 256: return run(k_attn<256>, k_attn_f32<256>);
-    case 128: return run(k_attn<128>, k_attn_f32<128>);
-    case 64: return run(k_attn<64>, k_attn_f32<64>);
+    case 256: return run(k_attn<256, false>, k_attn<256, true>);
+    case 128: return run(k_attn<128, false>, k_attn<128, true>);
+    case 64: return run(k_attn<64, false>, k_attn<64, true>);
     default: return hipErrorInvalidValue;
   }
 }

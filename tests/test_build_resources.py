@@ -27,7 +27,7 @@ def _report():
 # 32-key unit crossing the tail diagonal (a handful of units per workgroup). The
 # spill-free forms of that mask (masking inside the row max and the exponentials of
 # every unit) measured 6-7% slower over the whole update.
-ALLOWED_SCRATCH = {"_ZN2tu12_GLOBAL__N_16k_attnILi256E": 64, "_ZN2tu12_GLOBAL__N_110k_attn_f32ILi256E": 64}
+ALLOWED_SCRATCH = {"_ZN2tu12_GLOBAL__N_16k_attnILi256E": 64}
 
 
 def test_no_kernel_uses_scratch():
@@ -42,7 +42,7 @@ def test_lds_fits_a_cu():
 
 
 def test_attention_registers_fit_two_waves_per_simd():
-    att = {n: r for n, r in _report().items() if "k_attnILi" in n or "k_attn_f32ILi" in n}
+    att = {n: r for n, r in _report().items() if "k_attnILi" in n}
     assert len(att) == 6, sorted(att)      # head_dim 64, 128, 256; partial outputs in f16, in fp32
     for name, r in att.items():
         assert r["vgprs"] + r["agprs"] <= 256 and r["waves_per_simd"] >= 2, f"{name}: {r}"
